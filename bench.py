@@ -29,7 +29,8 @@ sys.path.insert(0, ROOT)
 
 METRIC = "SQ grid-pt*Chebyshev-steps/s & s/SCF iter, FP64 vs FP32-mixed at rho err 1e-5"
 HBM_PEAK_GBS = 8000.0
-KERNEL_SOURCE = os.path.join(ROOT, "paper_1708_07913_amd", "csrc", "sq_kernels.hip")
+KERNEL_SOURCES = [os.path.join(ROOT, "paper_1708_07913_amd", "csrc", f)
+                  for f in ("sq_kernels.hip", "sq_tile_kernels.hip", "sq_device.h")]
 
 
 def log(msg: str) -> None:
@@ -41,7 +42,7 @@ def kernel_hash() -> str:
     """Hash of the kernel code with comments and whitespace removed, so that a
     comment edit keeps the recorded counter traffic valid."""
     import re
-    text = open(KERNEL_SOURCE).read()
+    text = "\n".join(open(f).read() for f in KERNEL_SOURCES)
     text = re.sub(r"/\*.*?\*/", " ", text, flags=re.S)
     text = re.sub(r"//[^\n]*", " ", text)
     text = " ".join(text.split())

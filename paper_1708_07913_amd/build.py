@@ -42,6 +42,12 @@ CUBE_GROUPS = [[3, 5, 7, 9, 11, 13], [15, 17, 19], [21], [23], [25], [27], [29],
 # the two-row shapes of the 21-27-point cubes: a second build of the same
 # source (SQ_TWO_ROWS=1, kernels in namespace sq::two_rows)
 TWO_ROW_GROUPS = [[21], [23], [25], [27]]
+# Patch kernels (sq_tile_kernels.hip).  Every end of a branch restores the
+# execution mask by itself: with the compiler's pass that merges such ends, a
+# constant that was rematerialised after a masked loop fell in front of the
+# merged restore, was written with an empty mask, and a wild LDS address followed.
+TILE_CUBES = [25, 27, 29, 31]
+TILE_FLAGS = ["-mllvm", "-amdgpu-remove-redundant-endcf=0"]
 
 
 def _run(cmd):
@@ -64,6 +70,11 @@ def build(verbose: bool = False, jobs: int | None = None) -> str:
         obj = os.path.join(BUILD, f"sq_kernels_{i}.o")
         defs = [f"-DSQ_CUBES={cubes}", "-DSQ_PART=%d" % i, "-DSQ_TWO_ROWS=%d" % two]
         cmds.append([HIPCC, *DEVICE_FLAGS, *defs, "-c", src_k, "-o", obj])
+        objs.append(obj)
+    for c in reversed(TILE_CUBES):
+        obj = os.path.join(BUILD, f"sq_tile_{c}.o")
+        cmds.append([HIPCC, *DEVICE_FLAGS, *TILE_FLAGS, f"-DSQ_CUBES=X({c})", "-c", os.path.join(CSRC, "sq_tile_kernels.hip"),
+                     "-o", obj])
         objs.append(obj)
     obj = os.path.join(BUILD, "sq_common.o")
     cmds.append([HIPCC, *DEVICE_FLAGS, "-DSQ_COMMON_ONLY", "-c", src_k, "-o", obj])

@@ -56,6 +56,10 @@ struct sq_ctx {
     std::vector<sq::AtomDev> atoms;
     std::vector<sq::RunDev> runs;
     std::vector<double> pvals;
+    // patch kernels (tile): projector values on the grid, Lanczos start vector
+    // in thread order
+    bool tile = false;
+    std::vector<double> pgrid, start;
     std::vector<double> ctab, rk;
     double start_norm = 0;
     int device = 0;
@@ -65,7 +69,8 @@ struct sq_ctx {
     int max_overlap = 0;
     size_t off_atoms = 0, off_runs = 0, off_pvals = 0, off_chi = 0, off_zeta = 0, off_ctab = 0,
            off_rk = 0, off_W = 0, off_part = 0, off_scal = 0, off_flags = 0, off_forces = 0,
-           off_slots = 0, off_wslots = 0, off_xslots = 0, off_args = 0, total = 0;
+           off_slots = 0, off_wslots = 0, off_xslots = 0, off_args = 0, off_pgrid = 0,
+           off_start = 0, total = 0;
     sq::RecurrenceArgs args_host[2] = {};  // staged launch arguments (Lanczos, moments)
     char *ws = nullptr;
     const double *veff = nullptr;
@@ -196,6 +201,20 @@ int build_atom_table(sq_ctx *c, const double *R, double sig, double rc, double g
     return SQ_OK;
 }
 
+// Projector values on the periodic grid (patch kernels; no two spheres overlap).
+void build_projector_grid(sq_ctx *c) {
+    const long long n = c->n;
+    auto wrap = [n](long long v) { long long r = v % n; return r < 0 ? r + n : r; };
+    c->pgrid.assign(size_t(c->nd), 0.0);
+    for (const auto &at : c->atoms)
+        for (int r = 0; r < at.nrun; ++r) {
+            const sq::RunDev &run = c->runs[size_t(at.run0 + r)];
+            const long long col = wrap(at.bx + run.dx) + n * wrap(at.by + run.dy);
+            for (int k = 0; k < run.len; ++k)
+                c->pgrid[size_t(col + n * n * wrap(at.bz + run.dz0 + k))] = c->pvals[size_t(run.vstart + k * c->pstride)];
+        }
+}
+
 int hip_check(hipError_t e, const char *what) {
     if (e == hipSuccess) return SQ_OK;
     return fail(SQ_EDEVICE, std::string(what) + ": " + hipGetErrorString(e));
@@ -247,6 +266,8 @@ sq::RecurrenceArgs recurrence_args(sq_ctx *c) {
     a.ctab = c->at<double>(c->off_ctab);
     a.rk = c->at<double>(c->off_rk);
     a.kT = c->kT;
+    a.pgrid = c->at<double>(c->off_pgrid);
+    a.start = c->at<double>(c->off_start);
     return a;
 }
 
@@ -278,7 +299,7 @@ int pick_workgroups(sq_ctx *c) {
     if (rc) return rc;
     const bool mixed = c->opt.precision == SQ_FP32_MIXED;
     int bl = 0, bm = 0;
-    rc = hip_check(sq::recurrence_occupancy(c->C, true, false, c->nch, &bl), "occupancy (Lanczos)");
+    rc = hip_check(sq::recurrence_occupancy(c->C, true, mixed, c->nch, &bl), "occupancy (Lanczos)");
     if (rc) return rc;
     rc = hip_check(sq::recurrence_occupancy(c->C, false, mixed, c->nch, &bm), "occupancy (moments)");
     if (rc) return rc;
@@ -305,6 +326,8 @@ void layout(sq_ctx *c) {
     c->off_atoms = take(c->atoms.size() * sizeof(sq::AtomDev));
     c->off_runs = take(c->runs.size() * sizeof(sq::RunDev));
     c->off_pvals = take(c->pvals.size() * sizeof(double));
+    c->off_pgrid = take(c->pgrid.size() * sizeof(double));
+    c->off_start = take(c->start.size() * sizeof(double));
     c->off_chi = take(size_t(c->nd) * sizeof(double));
     c->off_zeta = take(size_t(c->nd) * sizeof(double));
     c->off_ctab = take(c->ctab.size() * sizeof(double));
@@ -528,7 +551,8 @@ int enqueue_recurrences(sq_batch *b, bool lanczos, bool moments, hipStream_t s, 
         const auto &g = b->groups[size_t(gi)];
         if (g.n_items == 0 || (only >= 0 && gi != only)) continue;
         rc = hip_check(
-            sq::launch_lanczos(group_launch(b, g, 2 * gi), g.C, g.nch, batch_grid(b, g, true), s, g.shape),
+            sq::launch_lanczos(group_launch(b, g, 2 * gi), g.C, g.nch, b->mixed, batch_grid(b, g, true), s,
+                               g.shape),
             "launching batched Lanczos");
         if (rc) return rc;
     }
@@ -935,6 +959,8 @@ int sq_setup(sq_ctx **ctx, double cell, double h, int fd_order, double rcut, int
             if (c->max_overlap > 2 && c->C > sq::kResidentCube)
                 return fail(SQ_ECAPACITY, "regions wider than 31 points support at most two overlapping projector spheres");
             c->nch = c->max_overlap > 2 ? 4 : (c->max_overlap > 1 ? 2 : 1);
+            c->tile = sq::tile_launch(c->C, c->nch, 0, c->opt.precision == SQ_FP32_MIXED);
+            if (c->tile) build_projector_grid(c.get());
         }
         // discrete-orthogonality table on N_q = n_pl + 1 Chebyshev-Gauss nodes
         c->ctab.assign(size_t(c->nq) * c->nq, 0.0);
@@ -945,12 +971,24 @@ int sq_setup(sq_ctx **ctx, double cell, double h, int fd_order, double rcut, int
             for (int k = 0; k < c->nq; ++k)
                 c->ctab[size_t(j) * c->nq + k] = (j == 0 ? 1.0 : 2.0) / c->nq * std::cos(j * pi * (k + 0.5) / c->nq);
         // Lanczos start vector: u(a) - 1/2, u(a) = (SplitMix64(a) >> 11) 2^-53
+        auto start_value = [](long long a) {
+            return double(splitmix64_first(uint64_t(a)) >> 11) * (1.0 / 9007199254740992.0) - 0.5;
+        };
         double s2 = 0.0;
         for (long long a = 0; a < c->ns; ++a) {
-            const double u = double(splitmix64_first(uint64_t(a)) >> 11) * (1.0 / 9007199254740992.0) - 0.5;
+            const double u = start_value(a);
             s2 += u * u;
         }
         c->start_norm = std::sqrt(s2);
+        if (c->tile) {
+            c->start.assign(size_t(c->C) * sq::patch_plane(c->C), 0.0);
+            const double rnorm = 1.0 / c->start_norm;
+            for (int z = 0; z < c->C; ++z)
+                for (int y = 0; y < c->C; ++y)
+                    for (int x = 0; x < c->C; ++x)
+                        c->start[size_t(z) * sq::patch_plane(c->C) + sq::patch_point(c->C, x, y)] =
+                            start_value(x + (long long)c->C * (y + (long long)c->C * z)) * rnorm;
+        }
         int rc = pick_workgroups(c.get());
         if (rc) return rc;
         layout(c.get());
@@ -983,6 +1021,8 @@ int sq_bind(sq_ctx *c, void *workspace, size_t bytes, const double *veff, void *
         int rc = put(c->off_atoms, c->atoms.data(), c->atoms.size() * sizeof(sq::AtomDev));
         if (!rc) rc = put(c->off_runs, c->runs.data(), c->runs.size() * sizeof(sq::RunDev));
         if (!rc) rc = put(c->off_pvals, c->pvals.data(), c->pvals.size() * sizeof(double));
+        if (!rc) rc = put(c->off_pgrid, c->pgrid.data(), c->pgrid.size() * sizeof(double));
+        if (!rc) rc = put(c->off_start, c->start.data(), c->start.size() * sizeof(double));
         if (!rc) rc = put(c->off_ctab, c->ctab.data(), c->ctab.size() * sizeof(double));
         if (!rc) rc = put(c->off_rk, c->rk.data(), c->rk.size() * sizeof(double));
         if (!rc) rc = upload_veff(c, veff, s);
@@ -1016,7 +1056,8 @@ int sq_spectral_bounds(sq_ctx *c, double *lmin, double *lmax, void *stream) {
         sq::LaunchArgs k;
         rc = stage_launch(c, a, 0, s, &k);
         if (rc) return rc;
-        rc = hip_check(sq::launch_lanczos(k, c->C, c->nch, c->nwg_lanczos, s), "launching Lanczos");
+        rc = hip_check(sq::launch_lanczos(k, c->C, c->nch, c->opt.precision == SQ_FP32_MIXED, c->nwg_lanczos, s),
+                       "launching Lanczos");
         if (rc) return rc;
         ++c->bounds_gen;
         rc = read_flags(c, s);
@@ -1264,7 +1305,7 @@ int sq_batch_create(sq_batch **out, sq_ctx *const *ctxs, int n, double *const *m
             const int variants = sq::shape_variants(g.C);
             for (int sh = 0; sh < 4; ++sh) {
                 if (sh & ~variants) continue;
-                rc = hip_check(sq::recurrence_occupancy(g.C, true, false, g.nch, &g.occ_lv[sh], sh),
+                rc = hip_check(sq::recurrence_occupancy(g.C, true, b->mixed, g.nch, &g.occ_lv[sh], sh),
                                "occupancy (Lanczos)");
                 if (!rc)
                     rc = hip_check(sq::recurrence_occupancy(g.C, false, b->mixed, g.nch, &g.occ_mv[sh], sh),

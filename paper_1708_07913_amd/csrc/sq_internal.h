@@ -42,7 +42,39 @@ constexpr long long slot_plane(int C, int two = 0) {
                              : (long long)((C + rows_per_thread(C, two) - 1) / rows_per_thread(C, two)) * C *
                                    rows_per_thread(C, two);
 }
-constexpr long long slot_elems_for(int C, int two = 0) { return (long long)C * slot_plane(C, two); }
+// FP64 recurrences of the patch kernels (sq_tile_kernels.hip): cubes of 25 points
+// and more whose spheres do not overlap.  Per recurrence step with 256
+// workgroups, ring kernels -> patch kernels (us; bounds, moments):
+//   25 points  27.4 22.2 -> 24.3 21.6
+//   27 points  32.4 26.0 -> 26.6 23.2
+//   29 points  40.4 35.2 -> 30.5 27.9
+//   31 points  44.1 40.3 -> 35.4 30.9
+// Below 25 points a patch would leave more lanes idle than it saves; with a
+// second projector layer the registers spill (29 points: 48.5 48.6 -> 59.0
+// 45.8).  FP32-mixed contexts keep the ring kernels for both: their rounding
+// turns a last bit of difference in a sum or in a bound into one of 6e-8 in the
+// density of single nodes, and the ring kernels' order of summation costs the
+// patch kernels what they gain (27 points: 30.2 against 27.7).
+constexpr bool tile_cube(int C, int nch) { return C >= 25 && C <= kResidentCube && nch == 1; }
+// A thread's patch there: two x-adjacent by kPatchRows y-adjacent cube columns.
+constexpr int kPatchRows = 2;
+constexpr int patch_y(int C) { return (C + kPatchRows - 1) / kPatchRows; }
+// Threads along x: an even number (see Tile::PE) that fills a wave on every SIMD.
+constexpr int patch_lanes(int C) { return 256 / patch_y(C) / 2 * 2; }
+constexpr int patch_block(int C) { return (patch_lanes(C) * patch_y(C) + 63) / 64 * 64; }
+// Doubles per plane of a workgroup's slot, and the element of a plane that
+// holds cube column (x, y): pairs along x are neighbours, patch row by patch
+// row, thread by thread.
+constexpr int patch_plane(int C) { return 2 * kPatchRows * patch_block(C); }
+constexpr int patch_point(int C, int x, int y) {
+    return 2 * ((y % kPatchRows) * patch_block(C) + y / kPatchRows * patch_lanes(C) + x / 2) + x % 2;
+}
+constexpr long long slot_elems_for(int C, int two = 0) {
+    return (long long)C * (tile_cube(C, 1) && slot_plane(C, two) < patch_plane(C) ? patch_plane(C) : slot_plane(C, two));
+}
+// Whether a launch of kernel shape `shape` runs the patch kernels (the default
+// shape of FP64 contexts does).
+constexpr bool tile_launch(int C, int nch, int shape, bool mixed) { return tile_cube(C, nch) && shape == 0 && !mixed; }
 
 // Kernel shape variants of the register-ring recurrence kernels (bit set):
 // two rows per thread (cubes with has_two_row_shape) and two planes per
@@ -55,6 +87,9 @@ constexpr bool has_two_plane_shape(int C) { return C >= 21 && C <= kResidentCube
 constexpr int shape_variants(int C) {
     return (has_two_row_shape(C) ? kShapeTwoRows : 0) | (has_two_plane_shape(C) ? kShapeTwoPlanes : 0);
 }
+
+// Projector runs of a region that the recurrence kernels accept.
+constexpr int max_region_runs(int C) { return (C > kResidentCube ? 4 : 6) * C * C + 512; }
 
 // One atom's projector, stored as z-runs: for every (dx, dy) column of the
 // sphere relative to the base node (bx, by, bz) = floor(R / h), the contiguous
@@ -108,6 +143,10 @@ struct RecurrenceArgs {
     const double *rk;       // n_pl + 1 Chebyshev-Gauss nodes
     double mu, kT;          // Fermi level, smearing (Ha)
     double *forces;         // natom x 3, accumulated
+    // patch kernels: projector values on the periodic grid, the Lanczos start
+    // vector in thread order
+    const double *pgrid;
+    const double *start;
 };
 
 constexpr int kMaxForceNq = 257;  // n_pl + 1 limit of the force kernel
@@ -282,11 +321,15 @@ struct FermiSnap {
 
 // Launchers (sq_kernels.hip).  Return hipSuccess or the launch error.
 // C is the cube side and nch the projector chains of every snapshot launched.
-// `shape`: kShape* bits (0 = the default shape); bits that cube side C does
+// `mixed`: of a context with FP32-mixed precision.  `shape`: kShape* bits (0 = the default shape); bits that cube side C does
 // not have return hipErrorInvalidValue.
-hipError_t launch_lanczos(const LaunchArgs &k, int C, int nch, int nwg, hipStream_t s, int shape = 0);
+hipError_t launch_lanczos(const LaunchArgs &k, int C, int nch, bool mixed, int nwg, hipStream_t s, int shape = 0);
 hipError_t launch_moments(const LaunchArgs &k, int C, int nch, bool mixed, int nwg, hipStream_t s, int shape = 0);
 hipError_t launch_forces(const LaunchArgs &k, int C, int nch, int nwg, hipStream_t s);
+// The patch kernels (cubes with tile_cube(C, nch)).
+hipError_t launch_tile_lanczos(const LaunchArgs &k, int C, int nwg, hipStream_t s);
+hipError_t launch_tile_moments(const LaunchArgs &k, int C, int nwg, hipStream_t s);
+hipError_t tile_occupancy(int C, bool lanczos, int *blocks_per_cu);
 hipError_t launch_zero_ints(int *p, int n, hipStream_t s);
 hipError_t launch_zero_doubles(double *p, int n, hipStream_t s);
 int recurrence_block(int C, int shape = 0);

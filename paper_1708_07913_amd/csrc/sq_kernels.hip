@@ -22,11 +22,7 @@
 // operand is widened to FP64 before it is used, so the arithmetic (stencil
 // sum, projector terms, update, dots) is FP64 and the one rounding per step
 // is the FP32 store of t^{k+1}.
-#include <hip/hip_runtime.h>
-
-#include "sq_internal.h"
-
-#include <math.h>
+#include "sq_device.h"
 
 #include <mutex>
 #include <type_traits>
@@ -94,7 +90,7 @@ struct Shape {
     static constexpr int IDLE_WRITE = ROWS * P;
     static constexpr int BLOCK = (NT + 63) / 64 * 64;
     static constexpr int NW = BLOCK / 64;
-    static constexpr int MAXRUNS = (C > kResidentCube ? 4 : 6) * CC + 512;
+    static constexpr int MAXRUNS = max_region_runs(C);
     // whole columns of the current vector stay in registers up to kResidentCube;
     // wider regions stream it through the workgroup's buffers with a window of
     // 2 NO + 2 planes in registers
@@ -110,7 +106,6 @@ struct Shape {
 // y = value base (value at plane z is pvals[y + z]).  The sentinel never
 // becomes active and never ends.
 constexpr unsigned kSentinelX = (0xFEu << 16) | (0xFFu << 8);
-constexpr unsigned kIdleOffset = 0x7FFFFF00u;  // beyond every buffer: loads read 0, stores drop
 
 template <int C, typename T, int NCH>
 struct Lds {
@@ -142,40 +137,6 @@ struct LanczosLds {
     double be[kMaxLanczos];
 };
 
-__device__ __forceinline__ int floor_div(int a, int b) {
-    int q = a / b;
-    return (a % b != 0 && ((a < 0) != (b < 0))) ? q - 1 : q;
-}
-__device__ __forceinline__ int ceil_div(int a, int b) { return -floor_div(-a, b); }
-__device__ __forceinline__ int pmod(int a, int n) {
-    int r = a % n;
-    return r < 0 ? r + n : r;
-}
-
-// Raw buffer access: SGPR descriptor + one VGPR byte offset + SGPR byte offset,
-// so that per-plane addresses stay scalar.  Out-of-range offsets read 0 and
-// drop stores (used for idle columns).
-typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void *p, long long bytes) {
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), (short)0, (int)bytes, 0x00020000);
-}
-template <typename T>
-__device__ __forceinline__ T bload(__amdgpu_buffer_rsrc_t r, unsigned voff, unsigned soff);
-template <>
-__device__ __forceinline__ double bload<double>(__amdgpu_buffer_rsrc_t r, unsigned voff, unsigned soff) {
-    return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, voff, soff, 0));
-}
-template <>
-__device__ __forceinline__ float bload<float>(__amdgpu_buffer_rsrc_t r, unsigned voff, unsigned soff) {
-    return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, voff, soff, 0));
-}
-__device__ __forceinline__ void bstore(double v, __amdgpu_buffer_rsrc_t r, unsigned voff, unsigned soff) {
-    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, voff, soff, 0);
-}
-__device__ __forceinline__ void bstore(float v, __amdgpu_buffer_rsrc_t r, unsigned voff, unsigned soff) {
-    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), r, voff, soff, 0);
-}
-
 // A thread's RB rows at one plane of a thread-interleaved slot (Lanczos ring
 // kernel): one 8- or 16-byte access per thread, so a wave moves one
 // contiguous, line-aligned block.  The moments ring kernel keeps one access
@@ -204,44 +165,6 @@ __device__ __forceinline__ void slot_store(const double (&v)[RB], __amdgpu_buffe
     }
 }
 
-// Keep a running sum materialised where it is updated.  Without this the
-// compiler sinks a chain of per-plane accumulations to its single use after
-// the unrolled sweep and keeps every operand live until then.  Emits nothing.
-__device__ __forceinline__ void pin(double &x) { asm volatile("" : "+v"(x)); }
-
-// A workgroup-uniform double, moved to SGPRs (VALU ops then take it as their
-// scalar operand instead of holding a copy per lane).
-__device__ __forceinline__ double uniform(double v) {
-    const int lo = __builtin_amdgcn_readfirstlane(__double2loint(v));
-    const int hi = __builtin_amdgcn_readfirstlane(__double2hiint(v));
-    return __hiloint2double(hi, lo);
-}
-
-// The thread index as a value the compiler cannot relate to earlier uses:
-// addresses derived from it are formed where they are needed instead of being
-// kept live (and spilled) through the unrolled sweeps.
-__device__ __forceinline__ int fresh_tid() {
-    int t = (int)threadIdx.x;
-    asm volatile("" : "+v"(t));
-    return t;
-}
-
-// Butterfly sum over the 64 lanes.  The lane index is made opaque so that the
-// permute addresses are formed here rather than hoisted and kept live (they
-// would otherwise occupy registers through the whole sweep).
-__device__ __forceinline__ double wave_sum(double v) {
-    int lane = (int)__lane_id();
-    asm volatile("" : "+v"(lane));
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-        const int src = (lane ^ off) << 2;
-        const int lo = __builtin_amdgcn_ds_bpermute(src, __double2loint(v));
-        const int hi = __builtin_amdgcn_ds_bpermute(src, __double2hiint(v));
-        v += __hiloint2double(hi, lo);
-    }
-    return v;
-}
-
 // Sum of (a, b) over the workgroup; the result is returned to every thread.
 template <int C, typename T, int NCH>
 __device__ __forceinline__ void block_sum2(Lds<C, T, NCH> &L, double &a, double &b, int tid) {
@@ -263,15 +186,6 @@ __device__ __forceinline__ void block_sum2(Lds<C, T, NCH> &L, double &a, double 
     a = uniform(L.bc[0]);
     b = uniform(L.bc[1]);
     __syncthreads();
-}
-
-// SplitMix64 (S. Vigna): first output for a given seed, mapped to [0, 1).
-__device__ __forceinline__ double unit_from_seed(unsigned long long seed) {
-    unsigned long long z = seed + 0x9E3779B97F4A7C15ULL;
-    z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ULL;
-    z = (z ^ (z >> 27)) * 0x94D049BB133111EBULL;
-    z = z ^ (z >> 31);
-    return (double)(z >> 11) * (1.0 / 9007199254740992.0);
 }
 
 __device__ __forceinline__ unsigned run_key(uint2 r, bool with_chain) {
@@ -652,12 +566,6 @@ __device__ __forceinline__ void chains_advance(Chain (&ch)[NCH], double *s_dst, 
     }
 }
 
-__device__ __forceinline__ void node_coords(long long q, int n, int &qi, int &qj, int &qk) {
-    qi = (int)(q % n);
-    qj = (int)((q / n) % n);
-    qk = (int)(q / ((long long)n * n));
-}
-
 // Projector dots of a vector given plane by plane: s[dst][I] += p_I . t, with
 // t(r, z) the value of the thread's column r at plane z.
 // AHEAD2 selects the two-plane look-ahead walk (Chain2); the moments kernel
@@ -773,43 +681,6 @@ __device__ __forceinline__ double stencil_sum(const PlaneView<C, T> &pv, const T
     }
     return acc[1] + acc[0];
 }
-
-// Snapshot arguments and work items are read through the constant address
-// space: their addresses are workgroup-uniform, so the fields load into SGPRs.
-typedef __attribute__((address_space(4))) const RecurrenceArgs *SnapPtr;
-typedef __attribute__((address_space(4))) const WorkItem *ItemPtr;
-
-// The nodes a workgroup processes: one static share of snaps[0] (every node
-// q0, q0 + qs, ... < q1 of one XCD's range), or items taken from the queue
-// until it is empty.
-struct WorkSource {
-    int round = 0;
-    template <typename LdsT>
-    __device__ __forceinline__ bool next(const LaunchArgs &K, LdsT &L, int tid, SnapPtr &Ap, long long &q0,
-                                         long long &q1, long long &qs) {
-        if (!K.items) {
-            if (round++) return false;
-            Ap = (SnapPtr)K.snaps;
-            const long long nd = Ap->nd;
-            const int xcd = blockIdx.x & 7, per = gridDim.x >> 3, lw = blockIdx.x >> 3;
-            q0 = nd * xcd / 8 + lw;
-            q1 = nd * (xcd + 1) / 8;
-            qs = per;
-            return true;
-        }
-        __syncthreads();
-        if (tid == 0) L.item = atomicAdd(K.counter, 1);
-        __syncthreads();
-        const int idx = __builtin_amdgcn_readfirstlane(L.item);
-        if (idx >= K.n_items) return false;
-        const ItemPtr it = (ItemPtr)K.items + idx;
-        Ap = (SnapPtr)K.snaps + it->snap;
-        q0 = it->q0;
-        q1 = it->q1;
-        qs = 1;
-        return true;
-    }
-};
 
 // ---------------------------------------------------------------------------
 // Chebyshev recurrence and moments (Sec. 3.2):
@@ -1015,62 +886,6 @@ __global__ __launch_bounds__(Shape<C>::BLOCK) void moments_kernel(LaunchArgs K) 
 // extreme eigenvalues of the tridiagonal by Sturm counts (a 32-point
 // multisection that ends on the bracket bisection reaches).
 // ---------------------------------------------------------------------------
-__device__ int sturm_count(int k, const double *a, const double *b, double x, double pivmin) {
-    int cnt = 0;
-    double d = a[0] - x;
-    if (fabs(d) < pivmin) d = -pivmin;
-    if (d < 0) ++cnt;
-    for (int i = 1; i < k; ++i) {
-        d = (a[i] - x) - b[i - 1] * b[i - 1] / d;
-        if (fabs(d) < pivmin) d = -pivmin;
-        if (d < 0) ++cnt;
-    }
-    return cnt;
-}
-
-// Point idx (0..31) of the 32 interior points that split [lo, hi] into 33
-// equal parts; the same expression serves the lanes that evaluate the points
-// and the lanes that take them over as the new bracket.
-__device__ __forceinline__ double split_point(double lo, double hi, int idx) {
-    return lo + (hi - lo) * ((double)(idx + 1) / 33.0);
-}
-
-// Extreme eigenvalues of the tridiagonal T_k by Sturm counts, on one wave:
-// lanes 0-31 bracket the smallest eigenvalue (count target 1), lanes 32-63
-// the largest (target k).  A round evaluates the count at 32 interior points
-// of the bracket and keeps the sub-interval where it first reaches the
-// target, which narrows the bracket 33-fold where bisection halves it.  The
-// invariant count(lo) < target <= count(hi) holds throughout; the bracket
-// shrinks until no interior point is left (adjacent doubles) and its upper
-// end is returned, as with bisection.  out[0] = min, out[1] = max.
-__device__ void sturm_extremes(int k, const double *a, const double *b, double *out, int lane) {
-    double lo = INFINITY, hi = -INFINITY, bmax2 = 0.0;
-    for (int i = 0; i < k; ++i) {
-        const double r = (i > 0 ? fabs(b[i - 1]) : 0.0) + (i < k - 1 ? fabs(b[i]) : 0.0);
-        lo = fmin(lo, a[i] - r);
-        hi = fmax(hi, a[i] + r);
-        if (i < k - 1) bmax2 = fmax(bmax2, b[i] * b[i]);
-    }
-    const double pivmin = 2.2250738585072014e-308 * fmax(bmax2, 1.0);
-    const int half = lane >> 5, j = lane & 31;
-    const int target = half ? k : 1;
-    for (int round = 0; round < 64; ++round) {
-        const double x = split_point(lo, hi, j);
-        const bool inside = (x > lo) & (x < hi);
-        const unsigned long long in_mask = __builtin_amdgcn_ballot_w64(inside);
-        if ((unsigned)(half ? in_mask >> 32 : in_mask) == 0u) break;  // uniform per half
-        const bool ge = inside ? sturm_count(k, a, b, x, pivmin) >= target : x >= hi;
-        const unsigned long long gm = __builtin_amdgcn_ballot_w64(ge);
-        const unsigned g32 = (unsigned)(half ? gm >> 32 : gm);
-        const int f = g32 ? __builtin_ctz(g32) : 32;  // first point with count >= target
-        const double nlo = f > 0 ? split_point(lo, hi, f - 1) : lo;
-        const double nhi = f < 32 ? split_point(lo, hi, f) : hi;
-        lo = nlo;
-        hi = nhi;
-    }
-    if (j == 0) out[half] = hi;
-}
-
 // Cubes wider than kResidentCube (narrower ones run lanczos_ring_kernel):
 // w_j (not yet divided by beta_j) sits in buffer X and v_{j-1} (as the stored
 // w_{j-1}) in buffer Y, both read with a look-ahead window and scaled on load.
@@ -3005,103 +2820,105 @@ static __device__ __align__(256) double scratch[kStaticScratchDoubles];
 #ifndef SQ_COMMON_ONLY
 // Launchers.  Resident cubes (up to kResidentCube) run the register-ring
 // kernels in FP64 and moments_mixed_kernel in FP32-mixed mode, built for
-// 1, 2 or 4 projector chains.  Streamed cubes are built with two chains only
-// (the host rejects deeper sphere overlaps there) and run the FP64 streamed
-// kernels in both precisions: with the current vector streamed through
-// memory, FP32 storage saves no registers, and its operand widening made the
-// mixed kernel slower than the FP64 one there.
-template <int c, typename F>
+// 1, 2 or 4 projector chains; where the patch kernels serve the default
+// shape (tile_launch), the single-chain kernels are built only where other
+// launches reach them.  Streamed cubes are built with two chains only (the host
+// rejects deeper sphere overlaps there) and run the FP64 streamed kernels in
+// both precisions: with the current vector streamed through memory, FP32
+// storage saves no registers, and its operand widening made the mixed kernel
+// slower than the FP64 one there.
+// `single`: single-chain launches reach these kernels (the FP64 moments of the
+// default shape run the patch kernels where tile_cube says so).
+template <int c, bool single, typename F>
 hipError_t with_chains(int nch, F &&f) {
     if constexpr (!Shape<c>::STREAM) {
-        if (nch <= 1) return f(std::integral_constant<int, 1>());
-        if (nch <= 2) return f(std::integral_constant<int, 2>());
-        if (nch <= 4) return f(std::integral_constant<int, 4>());
+        if constexpr (single || !tile_cube(c, 1)) {
+            if (nch <= 1) return f(std::integral_constant<int, 1>());
+        }
+        if (nch == 2) return f(std::integral_constant<int, 2>());
+        if (nch > 2 && nch <= 4) return f(std::integral_constant<int, 4>());
         return hipErrorInvalidValue;
     } else {
         if (nch <= 2) return f(std::integral_constant<int, 2>());
         return hipErrorInvalidValue;
     }
 }
-// Planes per barrier of the ring kernels for shape bits `shape`.
-template <int c, typename F>
-hipError_t with_planes(int shape, F &&f) {
+// Planes per barrier of the ring kernels for shape bits `shape`, and the chain
+// counts built for it.
+template <int c, bool single, typename F>
+hipError_t with_shape(int nch, int shape, F &&f) {
     if constexpr (has_two_plane_shape(c))
-        if (shape & kShapeTwoPlanes) return f(std::integral_constant<int, 2>());
-    return f(std::integral_constant<int, 1>());
+        if (shape & kShapeTwoPlanes)
+            return with_chains<c, true>(nch, [&](auto n) { return f(n, std::integral_constant<int, 2>()); });
+    return with_chains<c, single || SQ_TWO_ROWS>(nch, [&](auto n) { return f(n, std::integral_constant<int, 1>()); });
 }
 template <int c>
 hipError_t launch_lanczos_t(const LaunchArgs &a, int nch, int nwg, hipStream_t s, int shape) {
-    return with_chains<c>(nch, [&](auto ncht) {
-        constexpr int NCH = decltype(ncht)::value;
-        if constexpr (!Shape<c>::STREAM) {
-            return with_planes<c>(shape, [&](auto ppbt) {
-                constexpr int PPB = decltype(ppbt)::value;
-                hipLaunchKernelGGL((lanczos_ring_kernel<c, NCH, PPB>), dim3(nwg), dim3(Shape<c>::BLOCK), 0, s, a);
-                return hipGetLastError();
-            });
-        } else {
+    return with_shape<c, true>(nch, shape, [&](auto ncht, auto ppbt) {
+        constexpr int NCH = decltype(ncht)::value, PPB = decltype(ppbt)::value;
+        if constexpr (!Shape<c>::STREAM)
+            hipLaunchKernelGGL((lanczos_ring_kernel<c, NCH, PPB>), dim3(nwg), dim3(Shape<c>::BLOCK), 0, s, a);
+        else
             hipLaunchKernelGGL((lanczos_kernel<c, NCH>), dim3(nwg), dim3(Shape<c>::BLOCK), 0, s, a);
-            return hipGetLastError();
-        }
+        return hipGetLastError();
     });
 }
 // The FP32-mixed moments kernel has one plane per barrier (the two-plane bit
 // selects the FP64 moments sweep's variant only).
 template <int c>
 hipError_t launch_moments_t(const LaunchArgs &a, int nch, bool mixed, int nwg, hipStream_t s, int shape) {
-    return with_chains<c>(nch, [&](auto ncht) {
-        constexpr int NCH = decltype(ncht)::value;
-        if constexpr (!Shape<c>::STREAM) {
-            if (mixed) {
-                hipLaunchKernelGGL((moments_mixed_kernel<c, NCH>), dim3(nwg), dim3(Shape<c>::BLOCK), 0, s, a);
-                return hipGetLastError();
-            }
-            return with_planes<c>(shape, [&](auto ppbt) {
-                constexpr int PPB = decltype(ppbt)::value;
-                hipLaunchKernelGGL((moments_ring_kernel<c, NCH, PPB>), dim3(nwg), dim3(Shape<c>::BLOCK), 0, s, a);
+    if constexpr (!Shape<c>::STREAM)
+        if (mixed)
+            return with_chains<c, true>(nch, [&](auto ncht) {
+                hipLaunchKernelGGL((moments_mixed_kernel<c, decltype(ncht)::value>), dim3(nwg), dim3(Shape<c>::BLOCK), 0,
+                                   s, a);
                 return hipGetLastError();
             });
-        } else {
+    return with_shape<c, false>(nch, shape, [&](auto ncht, auto ppbt) {
+        constexpr int NCH = decltype(ncht)::value, PPB = decltype(ppbt)::value;
+        if constexpr (!Shape<c>::STREAM)
+            hipLaunchKernelGGL((moments_ring_kernel<c, NCH, PPB>), dim3(nwg), dim3(Shape<c>::BLOCK), 0, s, a);
+        else
             hipLaunchKernelGGL((moments_kernel<c, NCH>), dim3(nwg), dim3(Shape<c>::BLOCK), 0, s, a);
-            return hipGetLastError();
-        }
+        return hipGetLastError();
     });
 }
 #if !SQ_TWO_ROWS
 template <int c>
 hipError_t launch_forces_t(const LaunchArgs &a, int nch, int nwg, hipStream_t s) {
-    if constexpr (!Shape<c>::STREAM) {
-        return with_chains<c>(nch, [&](auto ncht) {
-            constexpr int NCH = decltype(ncht)::value;
+    return with_chains<c, true>(nch, [&](auto ncht) {
+        constexpr int NCH = decltype(ncht)::value;
+        if constexpr (!Shape<c>::STREAM)
             hipLaunchKernelGGL((forces_ring_kernel<c, NCH>), dim3(nwg), dim3(Shape<c>::BLOCK), 0, s, a);
-            return hipGetLastError();
-        });
-    } else {
-        return with_chains<c>(nch, [&](auto ncht) {
-            constexpr int NCH = decltype(ncht)::value;
+        else
             hipLaunchKernelGGL((forces_kernel<c, NCH>), dim3(nwg), dim3(Shape<c>::BLOCK), 0, s, a);
-            return hipGetLastError();
-        });
-    }
+        return hipGetLastError();
+    });
 }
 #endif
 template <int c>
 hipError_t occupancy_t(bool lanczos, bool mixed, int nch, int *nb, int shape) {
     const int B = Shape<c>::BLOCK;
-    return with_chains<c>(nch, [&](auto ncht) {
-        constexpr int NCH = decltype(ncht)::value;
-        if constexpr (!Shape<c>::STREAM) {
-            if (!lanczos && mixed) return hipOccupancyMaxActiveBlocksPerMultiprocessor(nb, moments_mixed_kernel<c, NCH>, B, 0);
-            return with_planes<c>(shape, [&](auto ppbt) {
-                constexpr int PPB = decltype(ppbt)::value;
-                if (lanczos)
-                    return hipOccupancyMaxActiveBlocksPerMultiprocessor(nb, lanczos_ring_kernel<c, NCH, PPB>, B, 0);
-                return hipOccupancyMaxActiveBlocksPerMultiprocessor(nb, moments_ring_kernel<c, NCH, PPB>, B, 0);
+    if (lanczos)
+        return with_shape<c, true>(nch, shape, [&](auto ncht, auto ppbt) {
+            constexpr int NCH = decltype(ncht)::value, PPB = decltype(ppbt)::value;
+            if constexpr (!Shape<c>::STREAM)
+                return hipOccupancyMaxActiveBlocksPerMultiprocessor(nb, lanczos_ring_kernel<c, NCH, PPB>, B, 0);
+            else
+                return hipOccupancyMaxActiveBlocksPerMultiprocessor(nb, lanczos_kernel<c, NCH>, B, 0);
+        });
+    if constexpr (!Shape<c>::STREAM)
+        if (mixed)
+            return with_chains<c, true>(nch, [&](auto ncht) {
+                return hipOccupancyMaxActiveBlocksPerMultiprocessor(nb, moments_mixed_kernel<c, decltype(ncht)::value>, B,
+                                                                    0);
             });
-        } else {
-            if (lanczos) return hipOccupancyMaxActiveBlocksPerMultiprocessor(nb, lanczos_kernel<c, NCH>, B, 0);
+    return with_shape<c, false>(nch, shape, [&](auto ncht, auto ppbt) {
+        constexpr int NCH = decltype(ncht)::value, PPB = decltype(ppbt)::value;
+        if constexpr (!Shape<c>::STREAM)
+            return hipOccupancyMaxActiveBlocksPerMultiprocessor(nb, moments_ring_kernel<c, NCH, PPB>, B, 0);
+        else
             return hipOccupancyMaxActiveBlocksPerMultiprocessor(nb, moments_kernel<c, NCH>, B, 0);
-        }
     });
 }
 
@@ -3159,6 +2976,39 @@ SQ_TWO_ROW_CUBES
 #undef X
 }  // namespace two_rows
 #undef X_RECURRENCE_DECL
+// cubes of the patch kernels (tile_cube), sq_tile_kernels.hip
+#define SQ_TILE_CUBES X(25) X(27) X(29) X(31)
+#define X(c)                                                                                     \
+    hipError_t tile_lanczos_c##c(const LaunchArgs &a, int nwg, hipStream_t s);                   \
+    hipError_t tile_moments_c##c(const LaunchArgs &a, int nwg, hipStream_t s);                   \
+    hipError_t tile_occupancy_c##c(bool lanczos, int *nb);
+SQ_TILE_CUBES
+#undef X
+
+hipError_t launch_tile_lanczos(const LaunchArgs &a, int C, int nwg, hipStream_t s) {
+    switch (C) {
+#define X(c) case c: return tile_lanczos_c##c(a, nwg, s);
+        SQ_TILE_CUBES
+#undef X
+        default: return hipErrorInvalidValue;
+    }
+}
+hipError_t launch_tile_moments(const LaunchArgs &a, int C, int nwg, hipStream_t s) {
+    switch (C) {
+#define X(c) case c: return tile_moments_c##c(a, nwg, s);
+        SQ_TILE_CUBES
+#undef X
+        default: return hipErrorInvalidValue;
+    }
+}
+hipError_t tile_occupancy(int C, bool lanczos, int *blocks_per_cu) {
+    switch (C) {
+#define X(c) case c: return tile_occupancy_c##c(lanczos, blocks_per_cu);
+        SQ_TILE_CUBES
+#undef X
+        default: return hipErrorInvalidValue;
+    }
+}
 
 int recurrence_block(int C, int shape) {
     if (shape & ~shape_variants(C)) return 0;
@@ -3180,6 +3030,7 @@ int recurrence_block(int C, int shape) {
 
 hipError_t recurrence_occupancy(int C, bool lanczos, bool mixed, int nch, int *blocks_per_cu, int shape) {
     if (shape & ~shape_variants(C)) return hipErrorInvalidValue;
+    if (tile_launch(C, nch, shape, mixed)) return tile_occupancy(C, lanczos, blocks_per_cu);
     if (shape & kShapeTwoRows) {
         switch (C) {
 #define X(c) case c: return two_rows::occupancy_c##c(lanczos, mixed, nch, blocks_per_cu, shape);
@@ -3196,8 +3047,9 @@ hipError_t recurrence_occupancy(int C, bool lanczos, bool mixed, int nch, int *b
     }
 }
 
-hipError_t launch_lanczos(const LaunchArgs &a, int C, int nch, int nwg, hipStream_t s, int shape) {
+hipError_t launch_lanczos(const LaunchArgs &a, int C, int nch, bool mixed, int nwg, hipStream_t s, int shape) {
     if (shape & ~shape_variants(C)) return hipErrorInvalidValue;
+    if (tile_launch(C, nch, shape, mixed)) return launch_tile_lanczos(a, C, nwg, s);
     if (shape & kShapeTwoRows) {
         switch (C) {
 #define X(c) case c: return two_rows::lanczos_c##c(a, nch, nwg, s, shape);
@@ -3216,6 +3068,7 @@ hipError_t launch_lanczos(const LaunchArgs &a, int C, int nch, int nwg, hipStrea
 
 hipError_t launch_moments(const LaunchArgs &a, int C, int nch, bool mixed, int nwg, hipStream_t s, int shape) {
     if (shape & ~shape_variants(C)) return hipErrorInvalidValue;
+    if (tile_launch(C, nch, shape, mixed)) return launch_tile_moments(a, C, nwg, s);
     if (shape & kShapeTwoRows) {
         switch (C) {
 #define X(c) case c: return two_rows::moments_c##c(a, nch, mixed, nwg, s, shape);
