@@ -35,6 +35,8 @@ bool is_finite(double v) { return std::isfinite(v); }
 enum State { kSetup = 0, kBound = 1, kBounds = 2 };
 
 constexpr int kReduceBlocks = 1024;
+// Fermi level rounds before the first look at the search's state
+constexpr int kBrentRounds = 12;
 
 size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
 
@@ -68,7 +70,7 @@ struct sq_ctx {
     int pstride = 0;    // doubles between a projector value and the one a plane above
     int max_overlap = 0;
     size_t off_atoms = 0, off_runs = 0, off_pvals = 0, off_chi = 0, off_zeta = 0, off_ctab = 0,
-           off_rk = 0, off_W = 0, off_part = 0, off_scal = 0, off_flags = 0, off_forces = 0,
+           off_rk = 0, off_W = 0, off_part = 0, off_scal = 0, off_brent = 0, off_flags = 0, off_forces = 0,
            off_slots = 0, off_wslots = 0, off_xslots = 0, off_args = 0, off_pgrid = 0,
            off_start = 0, total = 0;
     sq::RecurrenceArgs args_host[2] = {};  // staged launch arguments (Lanczos, moments)
@@ -333,6 +335,7 @@ void layout(sq_ctx *c) {
     c->off_ctab = take(c->ctab.size() * sizeof(double));
     c->off_rk = take(c->rk.size() * sizeof(double));
     c->off_W = take(size_t(c->nd) * c->nq * sizeof(double));
+    c->off_brent = take(sizeof(sq::BrentState));
     c->off_part = take(3 * kReduceBlocks * sizeof(double));
     c->off_scal = take(8 * sizeof(double));
     c->off_flags = take(64);
@@ -359,20 +362,6 @@ int device_scalars(sq_ctx *c, hipStream_t s, double *out, int count) {
                                       hipMemcpyDeviceToHost, s), "reading device scalars");
     if (rc) return rc;
     return hip_check(hipStreamSynchronize(s), "reduction");
-}
-
-int electron_count(sq_ctx *c, double mu, hipStream_t s, double *out) {
-    int rc = hip_check(sq::launch_count(c->at<double>(c->off_W), c->at<double>(c->off_chi),
-                                        c->at<double>(c->off_zeta), c->at<double>(c->off_rk), c->nd, c->nq, mu,
-                                        c->kT, c->at<double>(c->off_part), kReduceBlocks,
-                                        c->at<double>(c->off_scal), s),
-                       "electron count");
-    if (rc) return rc;
-    double v = 0;
-    rc = device_scalars(c, s, &v, 1);
-    if (rc) return rc;
-    *out = 2.0 * v;
-    return SQ_OK;
 }
 
 int check_ctx(const sq_ctx *c, int need) {
@@ -585,22 +574,22 @@ int enqueue_pass(sq_batch *b, bool bounds, hipStream_t s) {
         if (rc) return rc;
     }
     sq::BrentState *st = b->at<sq::BrentState>(b->off_state);
-    rc = hip_check(sq::launch_brent_begin(st, b->at<sq::BrentParams>(b->off_prm), b->at<double>(b->off_ext), n, s),
+    rc = hip_check(sq::launch_brent_begin(st, b->at<sq::BrentParams>(b->off_prm), {}, b->at<double>(b->off_ext), n, s),
                    "Fermi level");
     if (rc) return rc;
+    long long max_nd = 0;
+    for (sq_ctx *c : b->ctx) max_nd = std::max(max_nd, c->nd);
     // two bracket evaluations, then at most max_brent iterations
     for (int it = 0; it < b->max_brent + 2; ++it) {
-        rc = hip_check(sq::launch_count_batch(b->at<sq::FermiSnap>(b->off_fermi), st, n, b->at<double>(b->off_part),
-                                              kReduceBlocks, s),
+        rc = hip_check(sq::launch_fermi_round(b->at<sq::FermiSnap>(b->off_fermi), {}, st, n, max_nd,
+                                              b->at<double>(b->off_part), kReduceBlocks, s),
                        "electron count");
-        if (rc) return rc;
-        rc = hip_check(sq::launch_brent_feed(st, b->at<double>(b->off_part), kReduceBlocks, n, s), "Brent step");
         if (rc) return rc;
     }
     for (int i = 0; i < n; ++i) {
         sq_ctx *c = b->ctx[size_t(i)];
         const double h3 = c->h * c->h * c->h;
-        rc = hip_check(sq::launch_density(c->at<double>(c->off_W), c->at<double>(c->off_chi),
+        rc = hip_check(sq::launch_density(b->moments[size_t(i)], c->at<double>(c->off_ctab), c->at<double>(c->off_chi),
                                           c->at<double>(c->off_zeta), c->at<double>(c->off_rk), c->nd, c->nq, 0.0,
                                           &st[i].xb, c->kT, h3, b->rho[size_t(i)], c->at<double>(c->off_part),
                                           kReduceBlocks, c->at<double>(c->off_scal), s),
@@ -1116,20 +1105,30 @@ int sq_fermi_level(sq_ctx *c, const double *moments, double n_electrons, double 
                                          c->at<double>(c->off_part), kReduceBlocks, c->at<double>(c->off_scal), s),
                        "spectral extent");
         if (rc) return rc;
-        double ext[2];
-        rc = device_scalars(c, s, ext, 2);
-        if (rc) return rc;
         // Brent's method (inverse quadratic interpolation, secant, bisection)
-        // on f(mu) = N(mu) - N_e over the spectral bracket; the same state
-        // machine runs on the device for batched snapshots.
+        // on f(mu) = N(mu) - N_e over the spectral bracket, one launch a round;
+        // the state is read back when the search has most likely ended, and then
+        // every few rounds
+        sq::BrentState *st = c->at<sq::BrentState>(c->off_brent);
+        const sq::BrentParams prm{c->kT, n_electrons, c->opt.mu_xtol, c->opt.ne_rtol * n_electrons, c->opt.max_brent, 0};
+        rc = hip_check(sq::launch_brent_begin(st, nullptr, prm, c->at<double>(c->off_scal), 1, s), "Fermi level");
+        if (rc) return rc;
+        const sq::FermiSnap f{c->at<double>(c->off_W), c->at<double>(c->off_chi), c->at<double>(c->off_zeta),
+                              c->at<double>(c->off_rk), c->nd, c->nq, 0, c->kT};
         sq::BrentState b;
-        sq::brent_begin(b, ext[0], ext[1], c->kT, n_electrons, c->opt.mu_xtol, c->opt.ne_rtol * n_electrons,
-                        c->opt.max_brent);
-        while (b.phase >= sq::kBrentLow && b.phase <= sq::kBrentIterate) {
-            double count = 0.0;
-            rc = electron_count(c, b.mu_eval, s, &count);
+        // two bracket evaluations, then at most max_brent iterations
+        int rounds = kBrentRounds;
+        for (long long left = c->opt.max_brent + 2LL; left > 0; rounds = kBrentRounds / 2) {
+            for (int i = 0; i < rounds && left > 0; ++i, --left) {
+                rc = hip_check(sq::launch_fermi_round(nullptr, f, st, 1, c->nd, c->at<double>(c->off_part),
+                                                      kReduceBlocks, s),
+                               "electron count");
+                if (rc) return rc;
+            }
+            rc = hip_check(hipMemcpyAsync(&b, st, sizeof(b), hipMemcpyDeviceToHost, s), "reading the Fermi level");
+            if (!rc) rc = hip_check(hipStreamSynchronize(s), "Fermi level");
             if (rc) return rc;
-            sq::brent_feed(b, count);
+            if (b.phase < sq::kBrentLow || b.phase > sq::kBrentIterate) break;
         }
         if (b.phase == sq::kBrentDone) {
             *mu = b.xb;
@@ -1149,12 +1148,8 @@ int sq_density_energy(sq_ctx *c, const double *moments, double mu, double *rho, 
         if (!moments || !rho || !energies) return fail(SQ_EINVAL, "moments, rho (device) and energies (host) are required");
         if (!is_finite(mu)) return fail(SQ_EINVAL, "mu must be finite");
         hipStream_t s = static_cast<hipStream_t>(stream);
-        rc = hip_check(sq::launch_quadrature_weights(moments, c->at<double>(c->off_ctab), c->at<double>(c->off_W),
-                                                     c->nd, c->npl, s),
-                       "quadrature weights");
-        if (rc) return rc;
         const double h3 = c->h * c->h * c->h;
-        rc = hip_check(sq::launch_density(c->at<double>(c->off_W), c->at<double>(c->off_chi),
+        rc = hip_check(sq::launch_density(moments, c->at<double>(c->off_ctab), c->at<double>(c->off_chi),
                                           c->at<double>(c->off_zeta), c->at<double>(c->off_rk), c->nd, c->nq, mu,
                                           nullptr, c->kT, h3, rho, c->at<double>(c->off_part), kReduceBlocks,
                                           c->at<double>(c->off_scal), s),

@@ -172,8 +172,7 @@ struct LaunchArgs {
 
 // ---------------------------------------------------------------------------
 // Brent's method for the Fermi level (Sec. 3.2: N(mu) = N_e), written as a
-// state machine fed one electron count at a time, so that the host loop and
-// the device step kernel of batched snapshots run the same arithmetic.
+// state machine fed one electron count at a time.
 // ---------------------------------------------------------------------------
 #if defined(__HIP_DEVICE_COMPILE__) || defined(__HIPCC__)
 #define SQ_HD __host__ __device__
@@ -195,7 +194,8 @@ struct BrentState {
     double xa, xb, xc, fa, fb, fc, step, prev_step;
     double mu_eval;              // where the next count is to be taken
     double n_e, xtol, ftol;      // target, bracket half-width and |N - N_e| tolerances
-    int phase, it, max_it, pad;
+    int phase, it, max_it;
+    int ticket;                  // workgroups that have finished the pending count
 };
 
 // Bracket [ext_lo - 40 kT, ext_hi + 40 kT] around the scaled spectra of all nodes.
@@ -217,7 +217,7 @@ SQ_HD inline void brent_begin(BrentState &b, double ext_lo, double ext_hi, doubl
     b.phase = kBrentLow;
     b.it = 0;
     b.max_it = max_it;
-    b.pad = 0;
+    b.ticket = 0;
 }
 
 // Feed N(mu_eval).  Afterwards either phase is pending again with a new
@@ -311,7 +311,7 @@ SQ_HD inline void brent_feed(BrentState &b, double count) {
     b.phase = kBrentIterate;
 }
 
-// Per-snapshot inputs of the batched electron count.
+// Inputs of the electron count (W: launch_quadrature_weights).
 struct FermiSnap {
     const double *W, *chi, *zeta, *rk;
     long long nd;
@@ -336,6 +336,7 @@ int recurrence_block(int C, int shape = 0);
 hipError_t recurrence_occupancy(int C, bool lanczos, bool mixed, int nch, int *blocks_per_cu, int shape = 0);
 hipError_t launch_set_bounds(const double *lmin, const double *lmax, double *chi, double *zeta,
                              long long nd, double margin, hipStream_t s);
+// W[k][q], nodes innermost.
 hipError_t launch_quadrature_weights(const double *mom, const double *ctab, double *W,
                                      long long nd, int npl, hipStream_t s);
 hipError_t launch_extent(const double *chi, const double *zeta, long long nd, double *partials,
@@ -343,13 +344,10 @@ hipError_t launch_extent(const double *chi, const double *zeta, long long nd, do
 // out[0..1] = min, max of a - b over n entries (b may be null: of a).
 hipError_t launch_diff_extent(const double *a, const double *b, long long n, double *partials, int nblk,
                               double *out, hipStream_t s);
-hipError_t launch_count(const double *W, const double *chi, const double *zeta, const double *rk,
-                        long long nd, int nq, double mu, double kT, double *partials, int nblk,
-                        double *out, hipStream_t s);
 // mu_dev: if not null, mu is read from it (device) instead of `mu`.
-hipError_t launch_density(const double *W, const double *chi, const double *zeta, const double *rk,
-                          long long nd, int nq, double mu, const double *mu_dev, double kT, double h3,
-                          double *rho, double *partials, int nblk, double *out, hipStream_t s);
+hipError_t launch_density(const double *mom, const double *ctab, const double *chi, const double *zeta,
+                          const double *rk, long long nd, int nq, double mu, const double *mu_dev, double kT,
+                          double h3, double *rho, double *partials, int nblk, double *out, hipStream_t s);
 // Allocation-free density and energies: kernels use the library's static
 // device scratch (static_scratch: its device address on the current device,
 // looked up once per device, and its size).  *sums receives the device address
@@ -359,16 +357,16 @@ hipError_t static_scratch(double **ptr, size_t *bytes);
 hipError_t launch_density_static(const double *mom, const double *ctab, const double *chi, const double *zeta,
                                  const double *rk, long long nd, int nq, double mu, double kT, double h3,
                                  double *rho, double *scratch_ptr, double **sums, hipStream_t s);
-// Batched Fermi level: N(mu_eval) of every snapshot still iterating (grid
-// nblk x nsnap, the same per-snapshot partial sums as launch_count), then one
-// Brent step per snapshot.
+// Fermi level search of one snapshot (fs, prm null: `one`) or a batch: begin, then
+// rounds of one electron count and one Brent step each; a round of a search that
+// has ended does nothing.  partials: pstride doubles per snapshot.
 struct BrentParams {
     double kT, n_e, xtol, ftol;
     int max_it, pad;
 };
-hipError_t launch_brent_begin(BrentState *st, const BrentParams *prm, const double *ext, int nsnap, hipStream_t s);
-hipError_t launch_count_batch(const FermiSnap *fs, const BrentState *st, int nsnap, double *partials, int nblk,
-                              hipStream_t s);
-hipError_t launch_brent_feed(BrentState *st, const double *partials, int nblk, int nsnap, hipStream_t s);
+hipError_t launch_brent_begin(BrentState *st, const BrentParams *prm, const BrentParams &one, const double *ext,
+                              int nsnap, hipStream_t s);
+hipError_t launch_fermi_round(const FermiSnap *fs, const FermiSnap &one, BrentState *st, int nsnap, long long max_nd,
+                              double *partials, int pstride, hipStream_t s);
 
 }  // namespace sq

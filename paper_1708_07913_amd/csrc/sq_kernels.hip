@@ -2521,6 +2521,11 @@ __global__ __launch_bounds__(Shape<C>::BLOCK) void lanczos_ring_kernel(LaunchArg
 //   W_qk = sum_j c-table[j][k] rho_q^j,  c-table[j][k] = (2 - delta_j0)/N_q cos(j theta_k),
 // so that sum_j c_q^j rho_q^j = sum_k g(lambda_qk) W_qk with
 // lambda_qk = zeta_q r_k + chi_q (same quadrature, regrouped).
+//
+// W = (c-table)^T rho is a contraction of N_q x N_q with N_q x N_d, done on the
+// FP64 matrix cores in 16 x 16 tiles.  It is stored with the nodes innermost, so
+// that a wave of the electron count has one quadrature point and neighbouring
+// nodes: where the Fermi function is 0 for all of them the wave reads nothing.
 // ---------------------------------------------------------------------------
 __global__ void set_bounds_kernel(const double *lmin, const double *lmax, double *chi, double *zeta,
                                   long long nd, double margin) {
@@ -2541,28 +2546,86 @@ __global__ void zero_doubles_kernel(double *p, int n) {
     for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) p[i] = 0.0;
 }
 
-__global__ void weights_kernel(const double *mom, const double *ctab, double *W, long long nd, int npl) {
-    const int nq = npl + 1;
-    const long long total = nd * nq;
-    for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < total;
-         i += (long long)gridDim.x * blockDim.x) {
-        const long long q = i / nq;
-        const int k = (int)(i - q * nq);
-        const double *r = mom + q * nq;
-        double s = 0.0;
-        for (int j = 0; j < nq; ++j) s += ctab[j * nq + k] * r[j];
-        W[i] = s;
+constexpr int kRedBlock = 256;
+constexpr int kTileNodes = 64;  // nodes of a workgroup at a time: 16 per wave
+// N_q up to which the moments of kTileNodes nodes are staged in LDS (64 KB at an
+// odd row length); longer rows are read from memory
+constexpr int kStagedNq = 127;
+
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+
+constexpr int staged_bytes(int nq) { return nq <= kStagedNq ? kTileNodes * (nq | 1) * 8 : 0; }
+
+// Moments of nodes q0 .. q0 + kTileNodes - 1 into LDS, rows of nq | 1 doubles.
+__device__ __forceinline__ void stage_moments(const double *mom, double *rows, long long q0, long long nd, int nq) {
+    const int pitch = nq | 1, dn = kRedBlock / nq, dj = kRedBlock % nq;
+    int node = (int)threadIdx.x / nq, j = (int)threadIdx.x % nq;
+    const double *src = mom + q0 * nq;
+    const int total = (int)(nd - q0 < kTileNodes ? nd - q0 : kTileNodes) * nq;
+    for (int i = threadIdx.x; i < total; i += kRedBlock) {
+        rows[node * pitch + j] = src[i];
+        node += dn;
+        j += dj;
+        if (j >= nq) {
+            j -= nq;
+            ++node;
+        }
     }
 }
 
-__device__ __forceinline__ double fermi_fn(double x) { return 1.0 / (1.0 + exp(x)); }
-
-__device__ __forceinline__ double entropy_fn(double x) {
-    const double ax = fabs(x), e = exp(-ax);
-    return -(log1p(e) + ax * e / (1.0 + e));
+// W of a wave's 16 nodes: f(k0, w) for every 16 quadrature points; lane l holds in
+// w[r] the weight of node l % 16 at point k0 + 4 r + l / 16.  `row`: moments of
+// the lane's node, `valid`: the node exists.
+template <typename F>
+__device__ __forceinline__ void weight_tiles(const double *row, bool valid, const double *ctab, int nq, F &&f) {
+    const int l = threadIdx.x & 63, c = l & 15, g = l >> 4;
+    for (int k0 = 0; k0 < nq; k0 += 16) {
+        const int k = k0 + c;
+        const bool in = k < nq;
+        f64x4 w = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll 4
+        for (int j0 = 0; j0 < nq; j0 += 4) {
+            const int j = j0 + g;
+            const double a = in && j < nq ? ctab[j * nq + k] : 0.0;
+            const double b = valid && j < nq ? row[j] : 0.0;
+            w = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, w, 0, 0, 0);
+        }
+        f(k0, w);
+    }
 }
 
-constexpr int kRedBlock = 256;
+// W[k][q] of all nodes.  1.3e6 nodes, N_q 65: the moments are read and W written
+// once (1.35 GB).
+template <bool STAGED>
+__global__ __launch_bounds__(kRedBlock) void weights_kernel(const double *mom, const double *ctab, double *W,
+                                                            long long nd, int nq) {
+    extern __shared__ double rows[];
+    const int l = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const long long tiles = (nd + kTileNodes - 1) / kTileNodes;
+    for (long long t = blockIdx.x; t < tiles; t += gridDim.x) {
+        const long long q0 = t * kTileNodes, q = q0 + 16 * wave + (l & 15);
+        if (STAGED) {
+            __syncthreads();
+            stage_moments(mom, rows, q0, nd, nq);
+            __syncthreads();
+        }
+        const bool valid = q < nd;
+        const double *row = STAGED ? rows + (16 * wave + (l & 15)) * (nq | 1) : mom + (valid ? q : 0) * nq;
+        weight_tiles(row, valid, ctab, nq, [&](int k0, const f64x4 &w) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int k = k0 + 4 * r + (l >> 4);
+                if (valid && k < nq) W[k * nd + q] = w[r];
+            }
+        });
+    }
+}
+
+// Fermi function and entropy term of x = (lambda - mu) / kT.  Beyond |x| = 80 the
+// Fermi function is 0 or 1 and the entropy 0 to 1e-33, far below the last bit of
+// any sum: a wave whose lanes all lie there takes no exponential.
+constexpr double kFarX = 80.0;
+__device__ __forceinline__ double fermi_fn(double x) { return 1.0 / (1.0 + exp(x)); }
 
 __device__ __forceinline__ double block_reduce(double v, double *sh) {
     v = wave_sum(v);
@@ -2639,107 +2702,171 @@ __global__ __launch_bounds__(kRedBlock) void diff_extent_kernel(const double *a,
     }
 }
 
-__global__ void extent_final(const double *partials, int nblk, double *out) {
-    if (threadIdx.x == 0 && blockIdx.x == 0) {
-        double lo = INFINITY, hi = -INFINITY;
-        for (int i = 0; i < nblk; ++i) {
-            lo = fmin(lo, partials[2 * i]);
-            hi = fmax(hi, partials[2 * i + 1]);
+__global__ __launch_bounds__(kRedBlock) void extent_final(const double *partials, int nblk, double *out) {
+    __shared__ double sh[2 * (kRedBlock / 64)];
+    double lo = INFINITY, hi = -INFINITY;
+    for (int i = threadIdx.x; i < nblk; i += kRedBlock) {
+        lo = fmin(lo, partials[2 * i]);
+        hi = fmax(hi, partials[2 * i + 1]);
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+        lo = fmin(lo, __shfl_xor(lo, off, 64));
+        hi = fmax(hi, __shfl_xor(hi, off, 64));
+    }
+    const int w = threadIdx.x >> 6;
+    if ((threadIdx.x & 63) == 0) {
+        sh[2 * w] = lo;
+        sh[2 * w + 1] = hi;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int i = 0; i < kRedBlock / 64; ++i) {
+            lo = fmin(lo, sh[2 * i]);
+            hi = fmax(hi, sh[2 * i + 1]);
         }
         out[0] = lo;
         out[1] = hi;
     }
 }
 
-__global__ __launch_bounds__(kRedBlock) void count_kernel(const double *W, const double *chi,
-                                                          const double *zeta, const double *rk,
-                                                          long long nd, int nq, double mu, double kT,
-                                                          double *partials) {
-    __shared__ double sh[kRedBlock / 64];
-    const long long total = nd * nq;
-    double acc = 0.0;
-    for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < total;
-         i += (long long)gridDim.x * blockDim.x) {
-        const long long q = i / nq;
-        const int k = (int)(i - q * nq);
-        const double lam = zeta[q] * rk[k] + chi[q];
-        acc += fermi_fn((lam - mu) / kT) * W[i];
-    }
-    const double s = block_reduce(acc, sh);
-    if (threadIdx.x == 0) partials[blockIdx.x] = s;
-}
-
-// N(mu_eval) of every snapshot whose Brent search is pending (blockIdx.y =
-// snapshot); per snapshot the same partial sums as count_kernel.
-__global__ __launch_bounds__(kRedBlock) void count_batch_kernel(const FermiSnap *fs, const BrentState *st,
-                                                                double *partials) {
-    __shared__ double sh[kRedBlock / 64];
-    const int si = blockIdx.y;
-    const int ph = st[si].phase;
-    if (ph < kBrentLow || ph > kBrentIterate) return;
-    const FermiSnap f = fs[si];
-    const double mu = st[si].mu_eval;
-    const long long total = f.nd * f.nq;
-    double acc = 0.0;
-    for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < total;
-         i += (long long)gridDim.x * blockDim.x) {
-        const long long q = i / f.nq;
-        const int k = (int)(i - q * f.nq);
-        const double lam = f.zeta[q] * f.rk[k] + f.chi[q];
-        acc += fermi_fn((lam - mu) / f.kT) * f.W[i];
-    }
-    const double s = block_reduce(acc, sh);
-    if (threadIdx.x == 0) partials[(long long)si * gridDim.x + blockIdx.x] = s;
-}
-
-__global__ void brent_begin_kernel(BrentState *st, const BrentParams *prm, const double *ext, int nsnap) {
+__global__ void brent_begin_kernel(BrentState *st, const BrentParams *prm, BrentParams one, const double *ext,
+                                   int nsnap) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= nsnap) return;
-    const BrentParams p = prm[i];
+    const BrentParams p = prm ? prm[i] : one;
     BrentState b;
     brent_begin(b, ext[2 * i], ext[2 * i + 1], p.kT, p.n_e, p.xtol, p.ftol, p.max_it);
     st[i] = b;
 }
 
-// One Brent step per snapshot from the fixed-order sum of its partials
-// (N = 2 sum_q sum_k g(lambda_qk) W_qk).
-__global__ void brent_feed_kernel(BrentState *st, const double *partials, int nblk, int nsnap) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= nsnap) return;
-    BrentState b = st[i];
-    if (b.phase < kBrentLow || b.phase > kBrentIterate) return;
-    double sum = 0.0;
-    for (int j = 0; j < nblk; ++j) sum += partials[(long long)i * nblk + j];
-    brent_feed(b, 2.0 * sum);  // two electrons per state
-    st[i] = b;
+// One round of the Fermi level search: N(mu_eval) of every snapshot whose search
+// is pending (blockIdx.y = snapshot), then a Brent step by the workgroup that
+// finishes last (N = 2 sum_q sum_k g(lambda_qk) W_qk).  Every workgroup publishes
+// its sum and then takes a ticket; the last one adds them in a fixed order, so the
+// count does not depend on who is last, nor on the grid as long as every 64 nodes
+// have a workgroup of their own or the grid has kCountBlocks of them.
+constexpr int kCountBlocks = 1024;
+__global__ __launch_bounds__(kRedBlock) void fermi_round_kernel(const FermiSnap *fs, FermiSnap one, BrentState *st,
+                                                                double *partials, int pstride) {
+    __shared__ double sh[kRedBlock / 64];
+    __shared__ int last;
+    BrentState *bs = st + blockIdx.y;
+    const FermiSnap f = fs ? fs[blockIdx.y] : one;
+    const long long tiles = (f.nd + 63) / 64;
+    const int nblk = (int)(tiles < (long long)gridDim.x ? tiles : (long long)gridDim.x);
+    const int ph = bs->phase;
+    if (ph < kBrentLow || ph > kBrentIterate || (int)blockIdx.x >= nblk) return;
+    const double mu = bs->mu_eval, rkt = 1.0 / f.kT;
+    const int l = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    double acc = 0.0;
+    for (long long t = blockIdx.x; t < tiles; t += nblk) {
+        const long long q = t * 64 + l;
+        const bool valid = q < f.nd;
+        const long long qc = valid ? q : f.nd - 1;
+        const double z = f.zeta[qc], c = f.chi[qc];
+        const double *w = f.W + qc;
+        // wave w of the workgroup takes every fourth quadrature point, four at a time
+        for (int k0 = f.nq - 1 - wave; k0 >= 0; k0 -= 16) {
+            double x[4], wk[4];
+            bool on[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int k = k0 - 4 * u;
+                x[u] = k >= 0 ? (z * f.rk[k < 0 ? 0 : k] + c - mu) * rkt : 2.0 * kFarX;
+                on[u] = !__all(x[u] > kFarX);
+                wk[u] = on[u] ? w[k * f.nd] : 0.0;
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (on[u]) {
+                    const double g = __all(x[u] < -kFarX) ? 1.0 : fermi_fn(x[u]);
+                    acc += valid ? g * wk[u] : 0.0;
+                }
+        }
+    }
+    const double s = block_reduce(acc, sh);
+    double *mine = partials + (long long)blockIdx.y * pstride;
+    if (threadIdx.x == 0) {
+        __hip_atomic_store(&mine[blockIdx.x], s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        last = __hip_atomic_fetch_add(&bs->ticket, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == nblk - 1;
+    }
+    __syncthreads();
+    if (!last) return;
+    double v = 0.0;
+    for (int i = threadIdx.x; i < nblk; i += kRedBlock)
+        v += __hip_atomic_load(&mine[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const double sum = block_reduce(v, sh);
+    if (threadIdx.x == 0) {
+        BrentState b = *bs;
+        brent_feed(b, 2.0 * sum);  // two electrons per state
+        b.ticket = 0;
+        *bs = b;
+    }
 }
 
-__global__ __launch_bounds__(kRedBlock) void density_kernel(const double *W, const double *chi,
-                                                            const double *zeta, const double *rk,
-                                                            long long nd, int nq, double mu_arg,
-                                                            const double *mu_dev, double kT, double h3,
+// Density and energies straight from the moments: a wave forms W of 16 nodes on
+// the matrix cores and uses it where it stands, 4 quadrature points a lane; no
+// N_d x N_q buffer is written or read.  Per-block partials of {E_band, E_ent,
+// sum rho} go to `partials`.  1.3e6 nodes, N_q 65: bounded by the moments' bytes
+// (0.68 GB) and the contraction (0.19 ms each at this card's rates).
+template <bool STAGED>
+__global__ __launch_bounds__(kRedBlock) void density_kernel(const double *mom, const double *ctab, const double *chi,
+                                                            const double *zeta, const double *rk, long long nd, int nq,
+                                                            double mu_arg, const double *mu_dev, double kT, double h3,
                                                             double *rho, double *partials) {
+    extern __shared__ double rows[];
     __shared__ double sh[kRedBlock / 64];
-    const double mu = mu_dev ? *mu_dev : mu_arg;
+    const double mu = mu_dev ? *mu_dev : mu_arg, rkt = 1.0 / kT;
+    const int l = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const long long tiles = (nd + kTileNodes - 1) / kTileNodes;
     double eb = 0.0, en = 0.0, er = 0.0;
-    for (long long q = blockIdx.x * (long long)blockDim.x + threadIdx.x; q < nd;
-         q += (long long)gridDim.x * blockDim.x) {
-        const double c = chi[q], z = zeta[q];
-        const double *w = W + q * nq;
-        double sg = 0.0, sb = 0.0, se = 0.0;
-        for (int k = 0; k < nq; ++k) {
-            const double lam = z * rk[k] + c;
-            const double x = (lam - mu) / kT;
-            const double g = fermi_fn(x);
-            sg += g * w[k];
-            sb += lam * g * w[k];
-            se += entropy_fn(x) * w[k];
+    for (long long t = blockIdx.x; t < tiles; t += gridDim.x) {
+        const long long q0 = t * kTileNodes, q = q0 + 16 * wave + (l & 15);
+        if (STAGED) {
+            __syncthreads();
+            stage_moments(mom, rows, q0, nd, nq);
+            __syncthreads();
         }
-        const double r = 2.0 / h3 * sg;
-        rho[q] = r;
-        eb += 2.0 * sb;
-        en += 2.0 * kT * se;
-        er += r;
+        const bool valid = q < nd;
+        const long long qc = valid ? q : nd - 1;
+        const double c = chi[qc], z = zeta[qc];
+        const double *row = STAGED ? rows + (16 * wave + (l & 15)) * (nq | 1) : mom + qc * nq;
+        double sg = 0.0, sb = 0.0, se = 0.0;
+        weight_tiles(row, valid, ctab, nq, [&](int k0, const f64x4 &w) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int k = k0 + 4 * r + (l >> 4);
+                const bool in = k < nq;
+                const double lam = z * rk[in ? k : 0] + c, x = (lam - mu) * rkt;
+                double g, e;
+                if (__all(!in || fabs(x) > kFarX)) {
+                    g = x > 0.0 ? 0.0 : 1.0;
+                    e = 0.0;
+                } else {
+                    const double ax = fabs(x), ex = exp(-ax), d = 1.0 / (1.0 + ex);
+                    g = x > 0.0 ? ex * d : d;
+                    e = -(log1p(ex) + ax * ex * d);
+                }
+                if (in) {
+                    sg += g * w[r];
+                    sb += lam * g * w[r];
+                    se += e * w[r];
+                }
+            }
+        });
+        // a node's points lie in the four lanes 16 apart
+        sg += __shfl_xor(sg, 16, 64);
+        sg += __shfl_xor(sg, 32, 64);
+        if (valid) {
+            if (l < 16) {
+                const double v = 2.0 / h3 * sg;
+                rho[q] = v;
+                er += v;
+            }
+            eb += 2.0 * sb;
+            en += 2.0 * kT * se;
+        }
     }
     const double a = block_reduce(eb, sh);
     const double b = block_reduce(en, sh);
@@ -2751,55 +2878,14 @@ __global__ __launch_bounds__(kRedBlock) void density_kernel(const double *W, con
     }
 }
 
-// Fixed-order sum of `width` interleaved partial arrays (deterministic).
-__global__ void sum_partials(const double *partials, int nblk, int width, double *out) {
-    const int j = threadIdx.x;
-    if (blockIdx.x == 0 && j < width) {
-        double s = 0.0;
-        for (int i = 0; i < nblk; ++i) s += partials[width * i + j];
-        out[j] = s;
-    }
-}
-
-// Density and energies straight from the moments, for the allocation-free
-// entry point: the quadrature weights W_qk = sum_j c-table[j][k] rho_q^j of a
-// node are formed in registers (same sums, same order as weights_kernel), so
-// no N_d x N_q buffer is needed.  Per-block partials go to `partials`.
-__global__ __launch_bounds__(kRedBlock) void density_direct_kernel(const double *mom, const double *ctab,
-                                                                   const double *chi, const double *zeta,
-                                                                   const double *rk, long long nd, int nq,
-                                                                   double mu, double kT, double h3, double *rho,
-                                                                   double *partials) {
+// Sum of `width` interleaved partial arrays in a fixed order (one workgroup).
+__global__ __launch_bounds__(kRedBlock) void sum_partials(const double *partials, int nblk, int width, double *out) {
     __shared__ double sh[kRedBlock / 64];
-    double eb = 0.0, en = 0.0, er = 0.0;
-    for (long long q = blockIdx.x * (long long)blockDim.x + threadIdx.x; q < nd;
-         q += (long long)gridDim.x * blockDim.x) {
-        const double c = chi[q], z = zeta[q];
-        const double *r = mom + q * nq;
-        double sg = 0.0, sb = 0.0, se = 0.0;
-        for (int k = 0; k < nq; ++k) {
-            double w = 0.0;
-            for (int j = 0; j < nq; ++j) w += ctab[j * nq + k] * r[j];
-            const double lam = z * rk[k] + c;
-            const double x = (lam - mu) / kT;
-            const double g = fermi_fn(x);
-            sg += g * w;
-            sb += lam * g * w;
-            se += entropy_fn(x) * w;
-        }
-        const double rq = 2.0 / h3 * sg;
-        rho[q] = rq;
-        eb += 2.0 * sb;
-        en += 2.0 * kT * se;
-        er += rq;
-    }
-    const double a = block_reduce(eb, sh);
-    const double b = block_reduce(en, sh);
-    const double c = block_reduce(er, sh);
-    if (threadIdx.x == 0) {
-        partials[3 * blockIdx.x] = a;
-        partials[3 * blockIdx.x + 1] = b;
-        partials[3 * blockIdx.x + 2] = c;
+    for (int j = 0; j < width; ++j) {
+        double v = 0.0;
+        for (int i = threadIdx.x; i < nblk; i += kRedBlock) v += partials[width * i + j];
+        const double s = block_reduce(v, sh);
+        if (threadIdx.x == 0) out[j] = s;
     }
 }
 
@@ -3121,58 +3207,63 @@ hipError_t launch_zero_doubles(double *p, int n, hipStream_t s) {
     return hipGetLastError();
 }
 
+namespace {
+// Workgroups for the nodes of a launch, 64 to a workgroup at a time.
+int node_tiles(long long nd, int most) {
+    const long long t = (nd + kTileNodes - 1) / kTileNodes;
+    return (int)(t < most ? t : most);
+}
+}  // namespace
+
 hipError_t launch_quadrature_weights(const double *mom, const double *ctab, double *W, long long nd,
                                      int npl, hipStream_t s) {
-    hipLaunchKernelGGL(weights_kernel, dim3(grid_for(nd * (npl + 1), 256)), dim3(256), 0, s, mom, ctab, W,
-                       nd, npl);
+    const int nq = npl + 1;
+    const dim3 grid(node_tiles(nd, 1 << 20));
+    if (nq <= kStagedNq)
+        hipLaunchKernelGGL(weights_kernel<true>, grid, dim3(kRedBlock), staged_bytes(nq), s, mom, ctab, W, nd, nq);
+    else
+        hipLaunchKernelGGL(weights_kernel<false>, grid, dim3(kRedBlock), 0, s, mom, ctab, W, nd, nq);
     return hipGetLastError();
 }
 
 hipError_t launch_diff_extent(const double *a, const double *b, long long n, double *partials, int nblk,
                               double *out, hipStream_t s) {
     hipLaunchKernelGGL(diff_extent_kernel, dim3(nblk), dim3(kRedBlock), 0, s, a, b, n, partials);
-    hipLaunchKernelGGL(extent_final, dim3(1), dim3(64), 0, s, partials, nblk, out);
+    hipLaunchKernelGGL(extent_final, dim3(1), dim3(kRedBlock), 0, s, partials, nblk, out);
     return hipGetLastError();
 }
 
 hipError_t launch_extent(const double *chi, const double *zeta, long long nd, double *partials, int nblk,
                          double *out, hipStream_t s) {
     hipLaunchKernelGGL(extent_kernel, dim3(nblk), dim3(kRedBlock), 0, s, chi, zeta, nd, partials);
-    hipLaunchKernelGGL(extent_final, dim3(1), dim3(64), 0, s, partials, nblk, out);
+    hipLaunchKernelGGL(extent_final, dim3(1), dim3(kRedBlock), 0, s, partials, nblk, out);
     return hipGetLastError();
 }
 
-hipError_t launch_count(const double *W, const double *chi, const double *zeta, const double *rk,
-                        long long nd, int nq, double mu, double kT, double *partials, int nblk, double *out,
-                        hipStream_t s) {
-    hipLaunchKernelGGL(count_kernel, dim3(nblk), dim3(kRedBlock), 0, s, W, chi, zeta, rk, nd, nq, mu, kT,
-                       partials);
-    hipLaunchKernelGGL(sum_partials, dim3(1), dim3(64), 0, s, partials, nblk, 1, out);
+hipError_t launch_density(const double *mom, const double *ctab, const double *chi, const double *zeta,
+                          const double *rk, long long nd, int nq, double mu, const double *mu_dev, double kT,
+                          double h3, double *rho, double *partials, int nblk, double *out, hipStream_t s) {
+    const int grid = node_tiles(nd, nblk);
+    if (nq <= kStagedNq)
+        hipLaunchKernelGGL(density_kernel<true>, dim3(grid), dim3(kRedBlock), staged_bytes(nq), s, mom, ctab, chi,
+                           zeta, rk, nd, nq, mu, mu_dev, kT, h3, rho, partials);
+    else
+        hipLaunchKernelGGL(density_kernel<false>, dim3(grid), dim3(kRedBlock), 0, s, mom, ctab, chi, zeta, rk, nd, nq,
+                           mu, mu_dev, kT, h3, rho, partials);
+    hipLaunchKernelGGL(sum_partials, dim3(1), dim3(kRedBlock), 0, s, partials, grid, 3, out);
     return hipGetLastError();
 }
 
-hipError_t launch_density(const double *W, const double *chi, const double *zeta, const double *rk,
-                          long long nd, int nq, double mu, const double *mu_dev, double kT, double h3,
-                          double *rho, double *partials, int nblk, double *out, hipStream_t s) {
-    hipLaunchKernelGGL(density_kernel, dim3(nblk), dim3(kRedBlock), 0, s, W, chi, zeta, rk, nd, nq, mu, mu_dev,
-                       kT, h3, rho, partials);
-    hipLaunchKernelGGL(sum_partials, dim3(1), dim3(64), 0, s, partials, nblk, 3, out);
+hipError_t launch_brent_begin(BrentState *st, const BrentParams *prm, const BrentParams &one, const double *ext,
+                              int nsnap, hipStream_t s) {
+    hipLaunchKernelGGL(brent_begin_kernel, dim3((nsnap + 63) / 64), dim3(64), 0, s, st, prm, one, ext, nsnap);
     return hipGetLastError();
 }
 
-hipError_t launch_brent_begin(BrentState *st, const BrentParams *prm, const double *ext, int nsnap, hipStream_t s) {
-    hipLaunchKernelGGL(brent_begin_kernel, dim3((nsnap + 63) / 64), dim3(64), 0, s, st, prm, ext, nsnap);
-    return hipGetLastError();
-}
-
-hipError_t launch_count_batch(const FermiSnap *fs, const BrentState *st, int nsnap, double *partials, int nblk,
-                              hipStream_t s) {
-    hipLaunchKernelGGL(count_batch_kernel, dim3(nblk, nsnap), dim3(kRedBlock), 0, s, fs, st, partials);
-    return hipGetLastError();
-}
-
-hipError_t launch_brent_feed(BrentState *st, const double *partials, int nblk, int nsnap, hipStream_t s) {
-    hipLaunchKernelGGL(brent_feed_kernel, dim3((nsnap + 63) / 64), dim3(64), 0, s, st, partials, nblk, nsnap);
+hipError_t launch_fermi_round(const FermiSnap *fs, const FermiSnap &one, BrentState *st, int nsnap, long long max_nd,
+                              double *partials, int pstride, hipStream_t s) {
+    const dim3 grid(node_tiles(max_nd, kCountBlocks < pstride ? kCountBlocks : pstride), nsnap);
+    hipLaunchKernelGGL(fermi_round_kernel, grid, dim3(kRedBlock), 0, s, fs, one, st, partials, pstride);
     return hipGetLastError();
 }
 
@@ -3201,12 +3292,10 @@ hipError_t static_scratch(double **ptr, size_t *bytes) {
 hipError_t launch_density_static(const double *mom, const double *ctab, const double *chi, const double *zeta,
                                  const double *rk, long long nd, int nq, double mu, double kT, double h3,
                                  double *rho, double *scratch_ptr, double **sums, hipStream_t s) {
-    const int nblk = grid_for(nd, kRedBlock) < kStaticBlocks ? grid_for(nd, kRedBlock) : kStaticBlocks;
-    double *partials = scratch_ptr;
     double *out = scratch_ptr + 3 * kStaticBlocks;
-    hipLaunchKernelGGL(density_direct_kernel, dim3(nblk), dim3(kRedBlock), 0, s, mom, ctab, chi, zeta, rk, nd, nq,
-                       mu, kT, h3, rho, partials);
-    hipLaunchKernelGGL(sum_partials, dim3(1), dim3(64), 0, s, partials, nblk, 3, out);
+    const hipError_t e = launch_density(mom, ctab, chi, zeta, rk, nd, nq, mu, nullptr, kT, h3, rho, scratch_ptr,
+                                        kStaticBlocks, out, s);
+    if (e != hipSuccess) return e;
     *sums = out;
     return hipGetLastError();
 }
