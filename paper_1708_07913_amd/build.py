@@ -39,9 +39,9 @@ CXX = os.environ.get("CXX", "g++")
 # recurrence kernels are split into several translation units by cube size so
 # that the build parallelises
 CUBE_GROUPS = [[3, 5, 7, 9, 11, 13], [15, 17, 19], [21], [23], [25], [27], [29], [31], [33], [35], [37]]
-# the two-row shapes of the 21-27-point cubes: a second build of the same
+# the two-row kernels of the 17-27-point cubes: a second build of the same
 # source (SQ_TWO_ROWS=1, kernels in namespace sq::two_rows)
-TWO_ROW_GROUPS = [[21], [23], [25], [27]]
+TWO_ROW_GROUPS = [[17, 19], [21], [23], [25], [27]]
 # Patch kernels (sq_tile_kernels.hip).  Every end of a branch restores the
 # execution mask by itself: with the compiler's pass that merges such ends, a
 # constant that was rematerialised after a masked loop fell in front of the

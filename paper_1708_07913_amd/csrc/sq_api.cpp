@@ -65,7 +65,7 @@ struct sq_ctx {
     std::vector<double> ctab, rk;
     double start_norm = 0;
     int device = 0;
-    int nwg_lanczos = 0, nwg_moments = 0, nwg_slots = 0;
+    int nwg_lanczos = 0, nwg_moments = 0, nwg_forces = 0, nwg_slots = 0;
     int nch = 2;        // projector chains per cube column (max sphere overlap depth)
     int pstride = 0;    // doubles between a projector value and the one a plane above
     int max_overlap = 0;
@@ -300,21 +300,24 @@ int pick_workgroups(sq_ctx *c) {
     rc = hip_check(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev), "CU count");
     if (rc) return rc;
     const bool mixed = c->opt.precision == SQ_FP32_MIXED;
-    int bl = 0, bm = 0;
+    int bl = 0, bm = 0, bf = 0;
     rc = hip_check(sq::recurrence_occupancy(c->C, true, mixed, c->nch, &bl), "occupancy (Lanczos)");
     if (rc) return rc;
     rc = hip_check(sq::recurrence_occupancy(c->C, false, mixed, c->nch, &bm), "occupancy (moments)");
     if (rc) return rc;
-    if (bl < 1 || bm < 1) return fail(SQ_EDEVICE, "recurrence kernel does not fit on a compute unit");
+    rc = hip_check(sq::forces_occupancy(c->C, c->nch, &bf), "occupancy (forces)");
+    if (rc) return rc;
+    if (bl < 1 || bm < 1 || bf < 1) return fail(SQ_EDEVICE, "recurrence kernel does not fit on a compute unit");
     auto round8 = [](long long v) { return int(std::max<long long>(8, (v + 7) / 8 * 8)); };
     const long long cap = (c->nd + 7) / 8 * 8;
     if (c->opt.workgroups > 0) {
-        c->nwg_lanczos = c->nwg_moments = round8(c->opt.workgroups);
+        c->nwg_lanczos = c->nwg_moments = c->nwg_forces = round8(c->opt.workgroups);
     } else {
         c->nwg_lanczos = round8(std::min<long long>(cap, (long long)cus * bl / 8 * 8));
         c->nwg_moments = round8(std::min<long long>(cap, (long long)cus * bm / 8 * 8));
+        c->nwg_forces = round8(std::min<long long>(cap, (long long)cus * bf / 8 * 8));
     }
-    c->nwg_slots = std::max(c->nwg_lanczos, c->nwg_moments);
+    c->nwg_slots = std::max({c->nwg_lanczos, c->nwg_moments, c->nwg_forces});
     return SQ_OK;
 }
 
@@ -335,7 +338,6 @@ void layout(sq_ctx *c) {
     c->off_ctab = take(c->ctab.size() * sizeof(double));
     c->off_rk = take(c->rk.size() * sizeof(double));
     c->off_W = take(size_t(c->nd) * c->nq * sizeof(double));
-    c->off_brent = take(sizeof(sq::BrentState));
     c->off_part = take(3 * kReduceBlocks * sizeof(double));
     c->off_scal = take(8 * sizeof(double));
     c->off_flags = take(64);
@@ -347,8 +349,10 @@ void layout(sq_ctx *c) {
     // streamed regions (wider than kResidentCube) need a second buffer in the
     // moments sweep and a third in Lanczos
     const bool stream = c->C > sq::kResidentCube;
-    c->off_wslots = take(size_t(stream ? c->nwg_slots : c->nwg_lanczos) * se * sizeof(double));
-    c->off_xslots = take(stream ? size_t(c->nwg_lanczos) * se * sizeof(double) : 0);
+    const int nwg_two = std::max(c->nwg_lanczos, c->nwg_forces);  // launches with a second buffer
+    c->off_wslots = take(size_t(stream ? c->nwg_slots : nwg_two) * se * sizeof(double));
+    c->off_xslots = take(stream ? size_t(nwg_two) * se * sizeof(double) : 0);
+    c->off_brent = take(sizeof(sq::BrentState));
     c->total = off;
 }
 
@@ -1221,7 +1225,7 @@ int sq_nl_forces(sq_ctx *c, double mu, double *forces, void *stream) {
         sq::LaunchArgs k;
         rc = stage_launch(c, a, 1, s, &k);
         if (rc) return rc;
-        rc = hip_check(sq::launch_forces(k, c->C, c->nch, c->nwg_lanczos, s), "launching forces");
+        rc = hip_check(sq::launch_forces(k, c->C, c->nch, c->nwg_forces, s), "launching forces");
         if (rc) return rc;
         rc = hip_check(hipMemcpyAsync(forces, fdev, 3 * na * sizeof(double), hipMemcpyDeviceToHost, s),
                        "reading forces");

@@ -22,12 +22,23 @@ constexpr int kResidentCube = 31; // largest cube side whose columns stay in reg
 // two-row shape (`two` = 1: 32-lane row groups, 6-7 waves), built as a
 // separate set of kernels that batches may select (kShapeTwoRows).
 constexpr bool has_two_row_shape(int C) { return C >= 21 && C <= 27; }
+// Cubes whose FP64 recurrences run the two-row build by default.  One column a
+// thread is 5 to 7 waves, of which a CU holds one workgroup; two are 3 or 4, and
+// two workgroups share the CU and fill each other's waits (mesh of 20^3 or 16^3
+// nodes, 50 Lanczos steps and 16 moment steps, one column -> two, ms):
+//   17 points  20.9 5.7 -> 16.4 4.8
+//   19 points  23.9 6.6 -> 19.9 5.8
+//   21 points  14.8 4.1 -> 11.2 3.3
+// FP32-mixed contexts keep one column (its sums, see tile_cube).
+constexpr bool default_two_rows(int C) { return C >= 17 && C <= 21; }
 constexpr int rows_per_thread(int C, int two = 0) {
-    return C > kResidentCube ? 3 : (C >= 29 || (two && has_two_row_shape(C)) ? 2 : 1);
+    return C > kResidentCube ? 3 : (C >= 29 || (two && (has_two_row_shape(C) || default_two_rows(C))) ? 2 : 1);
 }
 // Threads per row group (lanes along x): two-row shapes give each row group
-// 32 lanes, the last ones idle.
+// 32 lanes, the last ones idle; those of 17-21 points C + 1, an even number, for
+// which a conflict-free row stride exists (see Shape::P).
 constexpr int row_group_threads(int C, int two = 0) {
+    if (two && default_two_rows(C)) return C + 1;
     return (C == 29 || C == 31 || (two && has_two_row_shape(C))) ? 32 : C;
 }
 // Doubles per plane of a workgroup's recurrence slot.  The Lanczos ring
@@ -70,6 +81,7 @@ constexpr int patch_point(int C, int x, int y) {
     return 2 * ((y % kPatchRows) * patch_block(C) + y / kPatchRows * patch_lanes(C) + x / 2) + x % 2;
 }
 constexpr long long slot_elems_for(int C, int two = 0) {
+    if (default_two_rows(C)) two = 1;  // the larger of the two layouts
     return (long long)C * (tile_cube(C, 1) && slot_plane(C, two) < patch_plane(C) ? patch_plane(C) : slot_plane(C, two));
 }
 // Whether a launch of kernel shape `shape` runs the patch kernels (the default
@@ -83,6 +95,10 @@ constexpr bool tile_launch(int C, int nch, int shape, bool mixed) { return tile_
 constexpr int kShapeTwoRows = 1;
 constexpr int kShapeTwoPlanes = 2;
 constexpr bool has_two_plane_shape(int C) { return C >= 21 && C <= kResidentCube; }
+// ... and the builds with kernels for it: the two-row build of 21 points runs its
+// one-plane kernels instead, whose half as many plane buffers leave room for a
+// second workgroup on the CU.
+constexpr bool two_plane_kernels(int C, int two) { return has_two_plane_shape(C) && !(two && default_two_rows(C)); }
 // Variants that exist for cube side C (a subset of the bits above).
 constexpr int shape_variants(int C) {
     return (has_two_row_shape(C) ? kShapeTwoRows : 0) | (has_two_plane_shape(C) ? kShapeTwoPlanes : 0);
@@ -326,6 +342,7 @@ struct FermiSnap {
 hipError_t launch_lanczos(const LaunchArgs &k, int C, int nch, bool mixed, int nwg, hipStream_t s, int shape = 0);
 hipError_t launch_moments(const LaunchArgs &k, int C, int nch, bool mixed, int nwg, hipStream_t s, int shape = 0);
 hipError_t launch_forces(const LaunchArgs &k, int C, int nch, int nwg, hipStream_t s);
+hipError_t forces_occupancy(int C, int nch, int *blocks_per_cu);
 // The patch kernels (cubes with tile_cube(C, nch)).
 hipError_t launch_tile_lanczos(const LaunchArgs &k, int C, int nwg, hipStream_t s);
 hipError_t launch_tile_moments(const LaunchArgs &k, int C, int nwg, hipStream_t s);

@@ -95,10 +95,13 @@ struct Shape {
     // wider regions stream it through the workgroup's buffers with a window of
     // 2 NO + 2 planes in registers
     static constexpr bool STREAM = C > kResidentCube;
-    // plane buffers: two for the streamed kernels (one plane per barrier);
-    // four for the register-ring kernels, which use two, or all four with
-    // two planes per barrier
-    static constexpr int NBUF = STREAM ? 2 : 4;
+    // plane buffers: two, or four where kernels with two planes per barrier
+    // exist (they use all four)
+    static constexpr int NBUF = !STREAM && two_plane_kernels(C, SQ_TWO_ROWS) ? 4 : 2;
+    // Waves of a SIMD that the register-ring kernels leave registers for (0: as
+    // many registers as the workgroup can have).  A recurrence step is a chain of barriers and LDS
+    // reads; in small cubes more workgroups on the CU fill its gaps.
+    static constexpr int WAVES = SQ_TWO_ROWS ? (default_two_rows(C) ? 2 : 0) : (C <= 11 ? 2 : (C <= 15 ? 3 : 0));
     static constexpr int CPT = (CC + BLOCK - 1) / BLOCK;     // columns per thread in the set-up scan
 };
 
@@ -107,24 +110,33 @@ struct Shape {
 // becomes active and never ends.
 constexpr unsigned kSentinelX = (0xFEu << 16) | (0xFFu << 8);
 
+// What only the set-up of a region needs.  Where LDS limits the workgroups of a
+// CU it lies over the plane buffers, which the set-up clears when it is done
+// with it, and the image offsets are short.
+template <int C>
+struct SetupLds {
+    int col_fill[Shape<C>::CC];
+    int img_prefix[kMaxImages + 1];
+    int img_run0[kMaxImages];
+    int img_nrun[kMaxImages];
+    int scan_tot[Shape<C>::NW];
+};
+struct NoSetupLds {};
+
 template <int C, typename T, int NCH>
 struct Lds {
     T plane[Shape<C>::NBUF][Shape<C>::PLANE];  // double-buffered groups of planes
     uint2 runs[Shape<C>::MAXRUNS + 1];
     int col_start[Shape<C>::CC + 1];
-    int col_fill[Shape<C>::CC];
     int col_off[Shape<C>::CC][NCH];  // first record of each chain, relative to col_start
     int img_atom[kMaxImages];
-    int img_lb[kMaxImages][3];
-    int img_prefix[kMaxImages + 1];
-    int img_run0[kMaxImages];
-    int img_nrun[kMaxImages];
+    std::conditional_t<(Shape<C>::WAVES > 1), short, int> img_lb[kMaxImages][3];
+    std::conditional_t<(Shape<C>::WAVES > 1), NoSetupLds, SetupLds<C>> setup;
     double img_coef[kMaxImages];
     double s[2][kMaxImages];
     double cs[kMaxImages];
     double red[Shape<C>::NW * 4];
     double bc[4];
-    int scan_tot[Shape<C>::NW];
     int ni;
     int bad;
     int nch;  // chains needed by this region (max sphere overlap depth, >= 1)
@@ -132,9 +144,10 @@ struct Lds {
     int item; // work-queue index taken by the workgroup
 };
 
+template <int N>
 struct LanczosLds {
-    double al[kMaxLanczos];
-    double be[kMaxLanczos];
+    double al[N];
+    double be[N];
 };
 
 // A thread's RB rows at one plane of a thread-interleaved slot (Lanczos ring
@@ -215,6 +228,15 @@ template <int C, typename T, int NCH, typename AT>
 __device__ void setup_region(const AT &A, Lds<C, T, NCH> &L, int qi, int qj, int qk, int tid) {
     using S = Shape<C>;
     const int n = A.n, m = A.m;
+    constexpr bool kOver = S::WAVES > 1;
+    static_assert(sizeof(SetupLds<C>) <= sizeof(L.plane), "set-up tables fit over the plane buffers");
+    SetupLds<C> &U = [&]() -> SetupLds<C> & {
+        if constexpr (kOver) return *reinterpret_cast<SetupLds<C> *>(&L.plane[0][0]);
+        else return L.setup;
+    }();
+    auto clear_planes = [&]() {
+        for (int i = tid; i < S::NBUF * S::PLANE; i += S::BLOCK) (&L.plane[0][0])[i] = T(0);
+    };
     if (tid == 0) {
         L.ni = 0;
         L.bad = 0;
@@ -222,8 +244,8 @@ __device__ void setup_region(const AT &A, Lds<C, T, NCH> &L, int qi, int qj, int
         L.ps = A.pstride;
         L.runs[S::MAXRUNS] = make_uint2(kSentinelX, 0u);
     }
-    for (int i = tid; i < S::NBUF * S::PLANE; i += S::BLOCK) (&L.plane[0][0])[i] = T(0);
-    for (int i = tid; i < S::CC; i += S::BLOCK) L.col_fill[i] = 0;
+    if constexpr (!kOver) clear_planes();
+    for (int i = tid; i < S::CC; i += S::BLOCK) U.col_fill[i] = 0;
     for (int i = tid; i < kMaxImages; i += S::BLOCK) L.s[0][i] = L.s[1][i] = 0.0;
     __syncthreads();
 
@@ -244,8 +266,8 @@ __device__ void setup_region(const AT &A, Lds<C, T, NCH> &L, int qi, int qj, int
                         L.img_lb[slot][1] = at.by + n * ty - lo1;
                         L.img_lb[slot][2] = at.bz + n * tz - lo2;
                         L.img_coef[slot] = at.coef;
-                        L.img_run0[slot] = at.run0;
-                        L.img_nrun[slot] = at.nrun;
+                        U.img_run0[slot] = at.run0;
+                        U.img_nrun[slot] = at.nrun;
                     }
                 }
     }
@@ -258,13 +280,13 @@ __device__ void setup_region(const AT &A, Lds<C, T, NCH> &L, int qi, int qj, int
     if (tid == 0) {
         int acc = 0;
         for (int i = 0; i < ni; ++i) {
-            L.img_prefix[i] = acc;
-            acc += L.img_nrun[i];
+            U.img_prefix[i] = acc;
+            acc += U.img_nrun[i];
         }
-        L.img_prefix[ni] = acc;
+        U.img_prefix[ni] = acc;
     }
     __syncthreads();
-    const int npairs = L.img_prefix[ni];
+    const int npairs = U.img_prefix[ni];
 
     // count, then place, the clipped z-runs of every image column inside the cube
     for (int pass = 0; pass < 2; ++pass) {
@@ -272,18 +294,18 @@ __device__ void setup_region(const AT &A, Lds<C, T, NCH> &L, int qi, int qj, int
             int lo = 0, hi = ni;  // largest I with prefix[I] <= p
             while (hi - lo > 1) {
                 const int mid = (lo + hi) >> 1;
-                if (L.img_prefix[mid] <= p) lo = mid;
+                if (U.img_prefix[mid] <= p) lo = mid;
                 else hi = mid;
             }
             const int I = lo;
-            const RunDev r = A.runs[L.img_run0[I] + (p - L.img_prefix[I])];
+            const RunDev r = A.runs[U.img_run0[I] + (p - U.img_prefix[I])];
             const int cx = L.img_lb[I][0] + r.dx, cy = L.img_lb[I][1] + r.dy;
             if (cx < 0 || cx >= C || cy < 0 || cy >= C) continue;
             const int z0 = L.img_lb[I][2] + r.dz0, z1 = z0 + r.len - 1;
             const int zl = z0 > 0 ? z0 : 0, zh = z1 < C - 1 ? z1 : C - 1;
             if (zl > zh) continue;
             const int col = cy * C + cx;
-            const int pos = atomicAdd(&L.col_fill[col], 1);
+            const int pos = atomicAdd(&U.col_fill[col], 1);
             if (pass == 1 && pos < S::MAXRUNS) {
                 L.runs[pos] = make_uint2((unsigned)I | ((unsigned)zl << 8) | ((unsigned)zh << 16),
                                          (unsigned)(r.vstart - z0 * A.pstride));
@@ -297,7 +319,7 @@ __device__ void setup_region(const AT &A, Lds<C, T, NCH> &L, int qi, int qj, int
             int chunk = 0;
 #pragma unroll
             for (int i = 0; i < S::CPT; ++i)
-                if (c0 + i < S::CC) chunk += L.col_fill[c0 + i];
+                if (c0 + i < S::CC) chunk += U.col_fill[c0 + i];
             int incl = chunk;
             const int lane = tid & 63;
 #pragma unroll
@@ -305,17 +327,17 @@ __device__ void setup_region(const AT &A, Lds<C, T, NCH> &L, int qi, int qj, int
                 const int t = __shfl_up(incl, off, 64);
                 if (lane >= off) incl += t;
             }
-            if (lane == 63) L.scan_tot[tid >> 6] = incl;
+            if (lane == 63) U.scan_tot[tid >> 6] = incl;
             __syncthreads();
             int base = 0;
-            for (int w = 0; w < (tid >> 6); ++w) base += L.scan_tot[w];
+            for (int w = 0; w < (tid >> 6); ++w) base += U.scan_tot[w];
             int run = base + incl - chunk;
 #pragma unroll
             for (int i = 0; i < S::CPT; ++i) {
                 if (c0 + i < S::CC) {
-                    const int v = L.col_fill[c0 + i];
+                    const int v = U.col_fill[c0 + i];
                     L.col_start[c0 + i] = run;
-                    L.col_fill[c0 + i] = run;
+                    U.col_fill[c0 + i] = run;
                     run += v;
                 }
             }
@@ -331,6 +353,7 @@ __device__ void setup_region(const AT &A, Lds<C, T, NCH> &L, int qi, int qj, int
         for (int i = tid; i <= S::CC; i += S::BLOCK) L.col_start[i] = 0;
         __syncthreads();
     }
+    if constexpr (kOver) clear_planes();
     // per column: sort by z_first, split first-fit into chains of disjoint runs
     // (as many as spheres overlap at one point), chain 0 first
     for (int col = tid; col < S::CC; col += S::BLOCK) {
@@ -900,7 +923,7 @@ __global__ __launch_bounds__(Shape<C>::BLOCK) void lanczos_kernel(LaunchArgs K) 
     constexpr int ZA = NO + 1;
     static_assert(S::STREAM, "streamed cubes only");
     __shared__ Lds<C, T, NCH> L;
-    __shared__ LanczosLds LL;
+    __shared__ LanczosLds<kMaxLanczos> LL;
     const int tid = threadIdx.x;
     Cols<C> cl;
     cl.init(tid);
@@ -1459,7 +1482,7 @@ __device__ __forceinline__ void moments_ring_sweep(const AT &A, Lds<C, double, N
 
 // PPB: planes per barrier of the sweeps (1 or 2).
 template <int C, int NCH, int PPB>
-__global__ __launch_bounds__(Shape<C>::BLOCK) void moments_ring_kernel(LaunchArgs K) {
+__global__ __launch_bounds__(Shape<C>::BLOCK, Shape<C>::WAVES) void moments_ring_kernel(LaunchArgs K) {
     using S = Shape<C>;
     constexpr int RB = S::RB;
     constexpr int MC = (C - 1) / 2;
@@ -1688,7 +1711,7 @@ __device__ void forces_gradient(const AT &A, const Lds<C, double, NCH> &L, Force
 
 
 template <int C, int NCH>
-__global__ __launch_bounds__(Shape<C>::BLOCK) void forces_ring_kernel(LaunchArgs K) {
+__global__ __launch_bounds__(Shape<C>::BLOCK, Shape<C>::WAVES) void forces_ring_kernel(LaunchArgs K) {
     using S = Shape<C>;
     constexpr int RB = S::RB;
     constexpr int MC = (C - 1) / 2;
@@ -2065,7 +2088,7 @@ __device__ __forceinline__ void mixed_sweep(const AT &A, Lds<C, double, NCH> &L,
 }
 
 template <int C, int NCH>
-__global__ __launch_bounds__(Shape<C>::BLOCK) void moments_mixed_kernel(LaunchArgs K) {
+__global__ __launch_bounds__(Shape<C>::BLOCK, Shape<C>::WAVES) void moments_mixed_kernel(LaunchArgs K) {
     using S = Shape<C>;
     constexpr int RB = S::RB;
     constexpr int MC = (C - 1) / 2;
@@ -2372,13 +2395,14 @@ __device__ __forceinline__ void lanczos_ring_sweep(const AT &A, Lds<C, double, N
 
 // PPB: planes per barrier of the sweeps (1 or 2).
 template <int C, int NCH, int PPB>
-__global__ __launch_bounds__(Shape<C>::BLOCK) void lanczos_ring_kernel(LaunchArgs K) {
+__global__ __launch_bounds__(Shape<C>::BLOCK, Shape<C>::WAVES) void lanczos_ring_kernel(LaunchArgs K) {
     using S = Shape<C>;
     constexpr int RB = S::RB;
     constexpr int NR = C + NO + 1;
     static_assert(!S::STREAM, "register ring: resident cubes only");
     __shared__ Lds<C, double, NCH> L;
-    __shared__ LanczosLds LL;
+    constexpr bool kInRegs = S::WAVES > 1;
+    __shared__ LanczosLds<kInRegs ? 1 : kMaxLanczos> LL;
     const int tid = threadIdx.x;
     Cols<C> cl;
     cl.init(tid);
@@ -2436,6 +2460,13 @@ __global__ __launch_bounds__(Shape<C>::BLOCK) void lanczos_ring_kernel(LaunchArg
         double al_m1 = 0.0, be_m2 = 0.0;    // alpha_{j-1}, beta_{j-2}
         double gersh = 0.0;
         int ksteps = kmax;
+        // alpha_j, beta_j: in LDS, or where LDS limits the workgroups of a CU in
+        // registers, those of j = tid, tid + BLOCK, ... (on 23 points, whose
+        // registers are scarce, that cost 4 %)
+        constexpr int NK = kInRegs ? (kMaxLanczos + S::BLOCK - 1) / S::BLOCK : 0;
+        double kal[NK + 1], kbe[NK + 1];
+#pragma unroll
+        for (int i = 0; i < NK; ++i) kal[i] = kbe[i] = 0.0;
         __syncthreads();
         // one step; returns false when the recurrence ends.  The ring layout
         // alternates, so steps are taken in (up, down) pairs and every pass of
@@ -2471,8 +2502,11 @@ __global__ __launch_bounds__(Shape<C>::BLOCK) void lanczos_ring_kernel(LaunchArg
             if (j >= 1) {
                 const double be = uniform(sqrt(dots[1]));  // beta_{j-1}
                 gersh = fmax(gersh, fabs(al_m1) + be + be_m2);
+#pragma unroll
+                for (int i = 0; i < NK; ++i)
+                    if (tid + i * S::BLOCK == j - 1) kbe[i] = be;
                 if (tid == 0) {
-                    LL.be[j - 1] = be;
+                    if constexpr (!kInRegs) LL.be[j - 1] = be;
                     if (!isfinite(be)) atomicOr(A.flags, kFlagLanczos);
                 }
                 if (be <= 1e-13 * gersh) {
@@ -2484,8 +2518,11 @@ __global__ __launch_bounds__(Shape<C>::BLOCK) void lanczos_ring_kernel(LaunchArg
             }
             const double al = j >= 1 ? uniform(sig * sig * (dots[0] + dots[3]) - sig_m1 * dots[2])
                                      : uniform(dots[0] + dots[3]);
+#pragma unroll
+            for (int i = 0; i < NK; ++i)
+                if (tid + i * S::BLOCK == j) kal[i] = al;
             if (tid == 0) {
-                LL.al[j] = al;
+                if constexpr (!kInRegs) LL.al[j] = al;
                 if (!isfinite(al)) atomicOr(A.flags, kFlagLanczos);
             }
             if (j == kmax - 1) return false;
@@ -2499,8 +2536,24 @@ __global__ __launch_bounds__(Shape<C>::BLOCK) void lanczos_ring_kernel(LaunchArg
             if (!step(j, std::true_type())) break;
             if (!step(j + 1, std::false_type())) break;
         }
+        const double *al = LL.al, *be = LL.be;
+        if constexpr (kInRegs) {
+            static_assert(sizeof(LanczosLds<kMaxLanczos>) <= sizeof(L.plane), "coefficients fit over the plane buffers");
+            double *pa = &L.plane[0][0], *pb = pa + kMaxLanczos;
+            __syncthreads();
+#pragma unroll
+            for (int i = 0; i < NK; ++i) {
+                const int k = tid + i * S::BLOCK;
+                if (k < kMaxLanczos) {
+                    pa[k] = kal[i];
+                    pb[k] = kbe[i];
+                }
+            }
+            al = pa;
+            be = pb;
+        }
         __syncthreads();
-        if (tid < 64) sturm_extremes(ksteps, LL.al, LL.be, L.bc, tid);
+        if (tid < 64) sturm_extremes(ksteps, al, be, L.bc, tid);
         __syncthreads();
         if (tid == 0) {
             const double lmn = L.bc[0], lmx = L.bc[1];
@@ -2933,7 +2986,7 @@ hipError_t with_chains(int nch, F &&f) {
 // counts built for it.
 template <int c, bool single, typename F>
 hipError_t with_shape(int nch, int shape, F &&f) {
-    if constexpr (has_two_plane_shape(c))
+    if constexpr (two_plane_kernels(c, SQ_TWO_ROWS))
         if (shape & kShapeTwoPlanes)
             return with_chains<c, true>(nch, [&](auto n) { return f(n, std::integral_constant<int, 2>()); });
     return with_chains<c, single || SQ_TWO_ROWS>(nch, [&](auto n) { return f(n, std::integral_constant<int, 1>()); });
@@ -2953,7 +3006,7 @@ hipError_t launch_lanczos_t(const LaunchArgs &a, int nch, int nwg, hipStream_t s
 // selects the FP64 moments sweep's variant only).
 template <int c>
 hipError_t launch_moments_t(const LaunchArgs &a, int nch, bool mixed, int nwg, hipStream_t s, int shape) {
-    if constexpr (!Shape<c>::STREAM)
+    if constexpr (!Shape<c>::STREAM && (!SQ_TWO_ROWS || has_two_row_shape(c)))
         if (mixed)
             return with_chains<c, true>(nch, [&](auto ncht) {
                 hipLaunchKernelGGL((moments_mixed_kernel<c, decltype(ncht)::value>), dim3(nwg), dim3(Shape<c>::BLOCK), 0,
@@ -2981,6 +3034,16 @@ hipError_t launch_forces_t(const LaunchArgs &a, int nch, int nwg, hipStream_t s)
         return hipGetLastError();
     });
 }
+template <int c>
+hipError_t forces_occupancy_t(int nch, int *nb) {
+    return with_chains<c, true>(nch, [&](auto ncht) {
+        constexpr int NCH = decltype(ncht)::value, B = Shape<c>::BLOCK;
+        if constexpr (!Shape<c>::STREAM)
+            return hipOccupancyMaxActiveBlocksPerMultiprocessor(nb, forces_ring_kernel<c, NCH>, B, 0);
+        else
+            return hipOccupancyMaxActiveBlocksPerMultiprocessor(nb, forces_kernel<c, NCH>, B, 0);
+    });
+}
 #endif
 template <int c>
 hipError_t occupancy_t(bool lanczos, bool mixed, int nch, int *nb, int shape) {
@@ -2993,7 +3056,7 @@ hipError_t occupancy_t(bool lanczos, bool mixed, int nch, int *nb, int shape) {
             else
                 return hipOccupancyMaxActiveBlocksPerMultiprocessor(nb, lanczos_kernel<c, NCH>, B, 0);
         });
-    if constexpr (!Shape<c>::STREAM)
+    if constexpr (!Shape<c>::STREAM && (!SQ_TWO_ROWS || has_two_row_shape(c)))
         if (mixed)
             return with_chains<c, true>(nch, [&](auto ncht) {
                 return hipOccupancyMaxActiveBlocksPerMultiprocessor(nb, moments_mixed_kernel<c, decltype(ncht)::value>, B,
@@ -3028,7 +3091,8 @@ hipError_t occupancy_t(bool lanczos, bool mixed, int nch, int *nb, int shape) {
     X_RECURRENCE(c)                                                                \
     hipError_t forces_c##c(const LaunchArgs &a, int nch, int nwg, hipStream_t s) { \
         return launch_forces_t<c>(a, nch, nwg, s);                                 \
-    }
+    }                                                                              \
+    hipError_t forces_occupancy_c##c(int nch, int *nb) { return forces_occupancy_t<c>(nch, nb); }
 #endif
 #ifdef SQ_CUBES
 SQ_CUBES
@@ -3051,11 +3115,12 @@ SQ_ALL_CUBES
     int block_c##c();
 #define X(c)          \
     X_RECURRENCE_DECL(c) \
-    hipError_t forces_c##c(const LaunchArgs &a, int nch, int nwg, hipStream_t s);
+    hipError_t forces_c##c(const LaunchArgs &a, int nch, int nwg, hipStream_t s); \
+    hipError_t forces_occupancy_c##c(int nch, int *nb);
 SQ_ALL_CUBES
 #undef X
-// cubes with a two-row build (has_two_row_shape)
-#define SQ_TWO_ROW_CUBES X(21) X(23) X(25) X(27)
+// cubes with a two-row build (has_two_row_shape, default_two_rows)
+#define SQ_TWO_ROW_CUBES X(17) X(19) X(21) X(23) X(25) X(27)
 namespace two_rows {
 #define X(c) X_RECURRENCE_DECL(c)
 SQ_TWO_ROW_CUBES
@@ -3096,6 +3161,12 @@ hipError_t tile_occupancy(int C, bool lanczos, int *blocks_per_cu) {
     }
 }
 
+// Whether a launch of kernel shape `shape` runs the two-row build: where that bit
+// is set, and for the FP64 default of default_two_rows.
+static bool two_row_launch(int C, int shape, bool mixed) {
+    return (shape & kShapeTwoRows) || (shape == 0 && !mixed && default_two_rows(C));
+}
+
 int recurrence_block(int C, int shape) {
     if (shape & ~shape_variants(C)) return 0;
     if (shape & kShapeTwoRows) {
@@ -3117,7 +3188,7 @@ int recurrence_block(int C, int shape) {
 hipError_t recurrence_occupancy(int C, bool lanczos, bool mixed, int nch, int *blocks_per_cu, int shape) {
     if (shape & ~shape_variants(C)) return hipErrorInvalidValue;
     if (tile_launch(C, nch, shape, mixed)) return tile_occupancy(C, lanczos, blocks_per_cu);
-    if (shape & kShapeTwoRows) {
+    if (two_row_launch(C, shape, mixed)) {
         switch (C) {
 #define X(c) case c: return two_rows::occupancy_c##c(lanczos, mixed, nch, blocks_per_cu, shape);
             SQ_TWO_ROW_CUBES
@@ -3136,7 +3207,7 @@ hipError_t recurrence_occupancy(int C, bool lanczos, bool mixed, int nch, int *b
 hipError_t launch_lanczos(const LaunchArgs &a, int C, int nch, bool mixed, int nwg, hipStream_t s, int shape) {
     if (shape & ~shape_variants(C)) return hipErrorInvalidValue;
     if (tile_launch(C, nch, shape, mixed)) return launch_tile_lanczos(a, C, nwg, s);
-    if (shape & kShapeTwoRows) {
+    if (two_row_launch(C, shape, mixed)) {
         switch (C) {
 #define X(c) case c: return two_rows::lanczos_c##c(a, nch, nwg, s, shape);
             SQ_TWO_ROW_CUBES
@@ -3155,7 +3226,7 @@ hipError_t launch_lanczos(const LaunchArgs &a, int C, int nch, bool mixed, int n
 hipError_t launch_moments(const LaunchArgs &a, int C, int nch, bool mixed, int nwg, hipStream_t s, int shape) {
     if (shape & ~shape_variants(C)) return hipErrorInvalidValue;
     if (tile_launch(C, nch, shape, mixed)) return launch_tile_moments(a, C, nwg, s);
-    if (shape & kShapeTwoRows) {
+    if (two_row_launch(C, shape, mixed)) {
         switch (C) {
 #define X(c) case c: return two_rows::moments_c##c(a, nch, mixed, nwg, s, shape);
             SQ_TWO_ROW_CUBES
@@ -3174,6 +3245,15 @@ hipError_t launch_moments(const LaunchArgs &a, int C, int nch, bool mixed, int n
 hipError_t launch_forces(const LaunchArgs &a, int C, int nch, int nwg, hipStream_t s) {
     switch (C) {
 #define X(c) case c: return forces_c##c(a, nch, nwg, s);
+        SQ_ALL_CUBES
+#undef X
+        default: return hipErrorInvalidValue;
+    }
+}
+
+hipError_t forces_occupancy(int C, int nch, int *blocks_per_cu) {
+    switch (C) {
+#define X(c) case c: return forces_occupancy_c##c(nch, blocks_per_cu);
         SQ_ALL_CUBES
 #undef X
         default: return hipErrorInvalidValue;
