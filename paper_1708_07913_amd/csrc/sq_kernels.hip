@@ -121,17 +121,14 @@ struct SetupLds {
     int img_nrun[kMaxImages];
     int scan_tot[Shape<C>::NW];
 };
-struct NoSetupLds {};
-
-template <int C, typename T, int NCH>
+template <int C, typename T, int NCH, bool OVER = (Shape<C>::WAVES > 1)>
 struct Lds {
     T plane[Shape<C>::NBUF][Shape<C>::PLANE];  // double-buffered groups of planes
     uint2 runs[Shape<C>::MAXRUNS + 1];
     int col_start[Shape<C>::CC + 1];
     int col_off[Shape<C>::CC][NCH];  // first record of each chain, relative to col_start
     int img_atom[kMaxImages];
-    std::conditional_t<(Shape<C>::WAVES > 1), short, int> img_lb[kMaxImages][3];
-    std::conditional_t<(Shape<C>::WAVES > 1), NoSetupLds, SetupLds<C>> setup;
+    short img_lb[kMaxImages][3];
     double img_coef[kMaxImages];
     double s[2][kMaxImages];
     double cs[kMaxImages];
@@ -142,6 +139,27 @@ struct Lds {
     int nch;  // chains needed by this region (max sphere overlap depth, >= 1)
     int ps;   // plane stride of the projector value boxes (doubles)
     int item; // work-queue index taken by the workgroup
+};
+
+template <int C, typename T, int NCH>
+struct Lds<C, T, NCH, false> {
+    T plane[Shape<C>::NBUF][Shape<C>::PLANE];
+    uint2 runs[Shape<C>::MAXRUNS + 1];
+    int col_start[Shape<C>::CC + 1];
+    int col_fill[Shape<C>::CC];
+    int col_off[Shape<C>::CC][NCH];
+    int img_atom[kMaxImages];
+    int img_lb[kMaxImages][3];
+    int img_prefix[kMaxImages + 1];
+    int img_run0[kMaxImages];
+    int img_nrun[kMaxImages];
+    double img_coef[kMaxImages];
+    double s[2][kMaxImages];
+    double cs[kMaxImages];
+    double red[Shape<C>::NW * 4];
+    double bc[4];
+    int scan_tot[Shape<C>::NW];
+    int ni, bad, nch, ps, item;
 };
 
 template <int N>
@@ -230,9 +248,9 @@ __device__ void setup_region(const AT &A, Lds<C, T, NCH> &L, int qi, int qj, int
     const int n = A.n, m = A.m;
     constexpr bool kOver = S::WAVES > 1;
     static_assert(sizeof(SetupLds<C>) <= sizeof(L.plane), "set-up tables fit over the plane buffers");
-    SetupLds<C> &U = [&]() -> SetupLds<C> & {
+    auto &U = [&]() -> auto & {
         if constexpr (kOver) return *reinterpret_cast<SetupLds<C> *>(&L.plane[0][0]);
-        else return L.setup;
+        else return L;
     }();
     auto clear_planes = [&]() {
         for (int i = tid; i < S::NBUF * S::PLANE; i += S::BLOCK) (&L.plane[0][0])[i] = T(0);
