@@ -705,14 +705,19 @@ __global__ __launch_bounds__(Tile<C>::BLOCK, 1) void moments_tile_kernel(LaunchA
 //   u_j = sigma_j H' x_j - beta_{j-1} sigma_{j-1} x_{j-1}
 //   alpha_j = s_j + alpha', alpha' = sigma_j u_j . x_j,
 //   beta_j^2 = |u_j|^2 - alpha'^2   (= |u_j - alpha' v_j|^2 with |v_j| = 1).
-// The shift keeps alpha' small beside beta_j, so the subtraction loses nothing
-// (alpha_j settles near the middle of the spectrum within a few steps); where it
-// would lose a digit, beta_j is summed from u_j - alpha' v_j itself.  The
-// projector dots of x_{j+1} follow from those of u_j and x_j in the same way.
+// The projector dots of x_{j+1} = u_j - alpha' v_j follow from those of u_j and
+// x_j in the same way.  A relative error of |x_j|^2 reaches beta_j^2 multiplied by
+// (alpha'/beta_j)^2, and one of the dots those of x_{j+1} multiplied by
+// |alpha'|/beta_j.  The shift keeps alpha' small beside beta_j (alpha_j settles near
+// the middle of the spectrum within a few steps).  Where it does not, as with a
+// V_eff of high and narrow peaks, the errors would grow from step to step: from
+// alpha'^2 > beta_j^2 / 4 on, both are summed from x_{j+1} itself (kCarried), and
+// below that line each step at least halves what it inherits.
 // Two vector transfers per step (x_{j-1} in, x_j out; the first planes in LDS);
 // 29-point cubes, 256 workgroups: 30.5 us a step (ring kernel, three transfers,
 // 40.4).
 // ---------------------------------------------------------------------------
+constexpr double kCarried = 0.8;  // least beta_j^2 / |u_j|^2 at which sums are carried: 1 / (1 + 1/4)
 struct TileLanczos {
     double al[kMaxLanczos];
     double be[kMaxLanczos];
@@ -758,21 +763,21 @@ __global__ __launch_bounds__(Tile<C>::BLOCK, 1) void lanczos_tile_kernel(LaunchA
             clear_prev<C, NPL>(L, tid);
             double coef[T::IPT], sx[T::IPT];  // sx: p_I . x_j
             image_coefs<C>(A, L, coef, tid);
-            // x_0 and its projector dots
-            {
+            // adds p_I . x to L.s, x given plane by plane: f(z, v) writes a plane of the
+            // thread's points
+            auto projector_dots = [&](auto &&f) {
                 double acc[T::NP];
 #pragma unroll
                 for (int r = 0; r < T::NP; ++r) acc[r] = 0.0;
-                const double *x0 = A.start + 2 * tid;
 #pragma unroll
                 for (int z = 0; z < C; ++z) {
                     const unsigned so = (unsigned)(n * n) * ((zbase + (unsigned)z) % (unsigned)n) * 8u;
+                    double x[T::NP];
+                    f(z, x);
 #pragma unroll
                     for (int r = 0; r < T::NP; ++r) {
-                        const double x = x0[(z * T::RY + (r >> 1)) * 2 * T::BLOCK + (r & 1)];
-                        X.v[z][r] = x;
                         const int i = pl.loff + z * T::LABZ + (r >> 1) * T::LW + (r & 1);
-                        acc[r] += bload<double>(pr, vcol[r], so) * x;
+                        acc[r] += bload<double>(pr, vcol[r], so) * x[r];
                         if (acc[r] != 0.0 && (z + 1 == C || L.lab[i] != L.lab[i + T::LABZ])) {
                             atomicAdd(&L.s[L.lab[i]], acc[r]);
                             acc[r] = 0.0;
@@ -780,6 +785,15 @@ __global__ __launch_bounds__(Tile<C>::BLOCK, 1) void lanczos_tile_kernel(LaunchA
                     }
                     __builtin_amdgcn_sched_barrier(0);
                 }
+            };
+            // x_0 and its projector dots
+            {
+                const double *x0 = A.start + 2 * tid;
+                projector_dots([&](int z, double(&x)[T::NP]) {
+#pragma unroll
+                    for (int r = 0; r < T::NP; ++r)
+                        X.v[z][r] = x[r] = x0[(z * T::RY + (r >> 1)) * 2 * T::BLOCK + (r & 1)];
+                });
             }
             __syncthreads();
 #pragma unroll
@@ -805,21 +819,26 @@ __global__ __launch_bounds__(Tile<C>::BLOCK, 1) void lanczos_tile_kernel(LaunchA
                 double b2 = d[0] - a1 * a1;
                 const double fa = uniform(a1 * sig);
                 const double al = uniform(shift + a1);
-                if (!(b2 > 0.1 * d[0]) && j + 1 < kmax) {
-                    // |u_j - alpha' v_j|^2 directly
+                const bool direct = !(b2 > kCarried * d[0]) && j + 1 < kmax;
+                if (direct) {
+                    // |x_{j+1}|^2 and p_I . x_{j+1} from x_{j+1} = u_j - alpha' v_j itself
                     double e[1] = {0.0};
 #pragma unroll
-                    for (int z = 0; z < C; ++z) {
+                    for (int i = 0; i < T::IPT; ++i) {
+                        const int I = tid + i * T::BLOCK;
+                        if (I < kMaxImages) L.s[I] = 0.0;
+                    }
+                    __syncthreads();  // every wave has read the first sums
+                    projector_dots([&](int z, double(&x)[T::NP]) {
                         double pv[T::NP];
                         prev_plane<C, NPL>(L, pl, slr, z, pv, tid);
 #pragma unroll
                         for (int r = 0; r < T::NP; ++r) {
-                            const double x = X.v[z][r] - fa * pv[r];
-                            e[0] += x * x;
+                            x[r] = X.v[z][r] - fa * pv[r];
+                            e[0] += x[r] * x[r];
                         }
                         pin(e[0]);
-                    }
-                    __syncthreads();  // every wave has read the first sums
+                    });
                     tile_sum<1, C>(L, e, tid);
                     b2 = e[0];
                 }
@@ -839,7 +858,7 @@ __global__ __launch_bounds__(Tile<C>::BLOCK, 1) void lanczos_tile_kernel(LaunchA
                 for (int i = 0; i < T::IPT; ++i) {
                     const int I = tid + i * T::BLOCK;
                     if (I < kMaxImages) {
-                        sx[i] = L.s[I] - fa * sx[i];
+                        sx[i] = direct ? L.s[I] : L.s[I] - fa * sx[i];
                         L.s[I] = 0.0;
                         L.cs[I] = rb * coef[i] * sx[i];
                     }
