@@ -382,16 +382,17 @@ __device__ __forceinline__ void tile_sweep(LdsT &L, const Place<C> &pl, Vec<C> &
             const double v[14] = {o[0].x, o[0].y, o[1].x, o[1].y, o[2].x, o[2].y, t[2 * b],
                                   t[2 * b + 1], o[3].x, o[3].y, o[4].x, o[4].y, o[5].x, o[5].y};
 #pragma unroll
-            for (int d = 1; d <= NO; ++d)
+            for (int d = NO; d >= 1; --d)
 #pragma unroll
                 for (int px = 0; px < 2; ++px) {
-                    fma_to(a[2 * b + px], kw[d], v[6 + px + d]);
-                    fma_to(a[2 * b + px], kw[d], v[6 + px - d]);
+                    // (the pair's own two come last)
+                    if (d > 1 || px == 1) fma_to(a[2 * b + px], kw[d], v[6 + px + d]);
+                    if (d > 1 || px == 0) fma_to(a[2 * b + px], kw[d], v[6 + px - d]);
                 }
         } else if (b == RY) {
             // row i + 1 below patch row 0
 #pragma unroll
-            for (int i = 0; i < NO; ++i)
+            for (int i = NO - 1; i >= 0; --i)
 #pragma unroll
                 for (int py = 0; py < RY; ++py) {
                     if (py + i + 1 > NO) continue;
@@ -399,9 +400,9 @@ __device__ __forceinline__ void tile_sweep(LdsT &L, const Place<C> &pl, Vec<C> &
                     fma_to(a[2 * py + 1], kw[py + i + 1], o[i].y);
                 }
         } else {
-            // row i above patch row RY - 1, then the patch's own rows
+            // row i above patch row RY - 1, then the patch's own neighbours
 #pragma unroll
-            for (int i = 0; i < NO; ++i)
+            for (int i = NO - 1; i >= 0; --i)
 #pragma unroll
                 for (int py = 0; py < RY; ++py) {
                     const int d = RY + i - py;
@@ -410,7 +411,10 @@ __device__ __forceinline__ void tile_sweep(LdsT &L, const Place<C> &pl, Vec<C> &
                     fma_to(a[2 * py + 1], kw[d], o[i].y);
                 }
 #pragma unroll
-            for (int r = 0; r < NP; ++r) fma_to(a[r], kw[1], t[(r + 2) % NP]);
+            for (int r = 0; r < NP; ++r) {
+                fma_to(a[r], kw[1], t[(r + 2) % NP]);
+                fma_to(a[r], kw[1], t[r ^ 1]);
+            }
         }
     };
     // z neighbours at distance d
@@ -448,11 +452,18 @@ __device__ __forceinline__ void tile_sweep(LdsT &L, const Place<C> &pl, Vec<C> &
         __syncthreads();  // plane z + 1
         const double(&t)[NP] = W[z % WN];
         if (z + 2 < C) publish(z + 2);
+        // The sum of a point grows from the smallest terms on: far legs first within each
+        // batch, the nearest ones at the end, the diagonal last.  One chain of 40 terms
+        // that starts with the diagonal has 1.2-1.5 times the rounding error of the ring
+        // kernels' tree of pair sums (and 2.4 times where V_eff is deep); in this order it
+        // has the same.  (Zeros behind the pin keep the chain's start here; a first
+        // product moved into the batches spilled.)
 #pragma unroll
-        for (int r = 0; r < NP; ++r) {
-            a[r] = vz[r] * t[r];
-            fma_to(a[r], st.c0, t[r]);
-        }
+        for (int r = 0; r < NP; ++r) a[r] = 0.0;
+        pin_all(a);
+        double dv[NP];
+#pragma unroll
+        for (int r = 0; r < NP; ++r) dv[r] = (vz[r] + st.c0) * t[r];
         if (z + 1 < C) load_potential();
 #pragma unroll
         for (int b = 0; b < NB; ++b) {
@@ -460,10 +471,12 @@ __device__ __forceinline__ void tile_sweep(LdsT &L, const Place<C> &pl, Vec<C> &
             if (b + 1 < NB) batch(z, b + 1);
             else if (z + 1 < C) batch(z + 1, 0);
 #pragma unroll
-            for (int d = 1 + b * NO / NB; d <= (b + 1) * NO / NB; ++d) legs_z(z, d);
+            for (int d = NO - b * NO / NB; d > NO - (b + 1) * NO / NB; --d) legs_z(z, d);
             legs(z, b);
             __builtin_amdgcn_sched_barrier(0);
         }
+#pragma unroll
+        for (int r = 0; r < NP; ++r) a[r] += dv[r];
         double out[NP];
 #pragma unroll
         for (int r = 0; r < NP; ++r) {
