@@ -859,7 +859,8 @@ __global__ __launch_bounds__(Tile<C>::BLOCK, 1) void lanczos_tile_kernel(LaunchA
                 if (tid == 0) {
                     LL.al[j] = al;
                     LL.be[j] = be;
-                    if (!isfinite(al) || !isfinite(be)) atomicOr(A.flags, kFlagLanczos);
+                    // (the last step's beta is not used)
+                    if (!isfinite(al) || (j + 1 < kmax && !isfinite(be))) atomicOr(A.flags, kFlagLanczos);
                 }
                 gersh = fmax(gersh, fabs(al) + be + bprev);
                 if (j == kmax - 1 || be <= 1e-13 * gersh) {

@@ -60,3 +60,17 @@ def test_bounds_of_peaked_potential(cube, steps, tol):
     scale = max(np.abs(lo_ref).max(), np.abs(hi_ref).max())
     assert np.abs(lo - lo_ref).max() < tol * scale
     assert np.abs(hi - hi_ref).max() < tol * scale
+
+
+def test_one_step_at_the_range_of_doubles():
+    """One Lanczos step has no beta: |u|^2 past the largest double is no error."""
+    from paper_1708_07913_amd import sq
+    wl = patch_cell(29)
+    V = np.where(np.arange(wl.n ** 3) % 3 == 0, 1e160, -2e160)
+    g = sq.SQ.from_workload(wl, veff=torch.from_numpy(V).cuda(), n_lanczos=1)
+    assert_patch_kernels(g, wl, 29)
+    nodes = np.array([0, 1, 1234, g.nd - 1])
+    lo, hi = (t.cpu().numpy()[nodes] for t in g.spectral_bounds())
+    lo_ref, hi_ref = oracle.Oracle.from_workload(wl, veff=V, n_lanczos=1).bounds(nodes=nodes)
+    assert np.isfinite(lo_ref).all()
+    assert np.abs(lo - lo_ref).max() < 1e-12 * 2e160 and np.abs(hi - hi_ref).max() < 1e-12 * 2e160
