@@ -2692,10 +2692,13 @@ __global__ __launch_bounds__(kRedBlock) void weights_kernel(const double *mom, c
     }
 }
 
-// Fermi function and entropy term of x = (lambda - mu) / kT.  Beyond |x| = 80 the
-// Fermi function is 0 or 1 and the entropy 0 to 1e-33, far below the last bit of
-// any sum: a wave whose lanes all lie there takes no exponential.
-constexpr double kFarX = 80.0;
+// Fermi function g and entropy term of x = (lambda - mu) / kT.  A wave whose lanes
+// all lie far from 0 takes no exponential.  Up to x = -kOneX, 1 + exp(x) rounds to 1,
+// so g is 1; beyond |x| = kZeroX, exp(-|x|) is 0, so g is 0 or 1 and the entropy 0.
+// The density takes mu as it is given, also far outside the spectrum, where every
+// term is small: it leaves out only what is exactly 0.
+constexpr double kOneX = 37.0, kZeroX = 746.0;
+__device__ __forceinline__ double reciprocal_kt(double kT) { return fmin(1.0 / kT, 1.7976931348623157e308); }
 __device__ __forceinline__ double fermi_fn(double x) { return 1.0 / (1.0 + exp(x)); }
 
 __device__ __forceinline__ double block_reduce(double v, double *sh) {
@@ -2828,7 +2831,11 @@ __global__ __launch_bounds__(kRedBlock) void fermi_round_kernel(const FermiSnap 
     const int nblk = (int)(tiles < (long long)gridDim.x ? tiles : (long long)gridDim.x);
     const int ph = bs->phase;
     if (ph < kBrentLow || ph > kBrentIterate || (int)blockIdx.x >= nblk) return;
-    const double mu = bs->mu_eval, rkt = 1.0 / f.kT;
+    const double mu = bs->mu_eval, rkt = reciprocal_kt(f.kT);
+    // Points that are left out: the weights of a node sum to 1 (their magnitudes to little
+    // more), so with far - log(N_d / N_e)
+    // = 60 all of them together change N by about 1e-26 N_e.
+    const double far = fmin(60.0 + log((double)f.nd / bs->n_e), kZeroX);
     const int l = threadIdx.x & 63, wave = threadIdx.x >> 6;
     double acc = 0.0;
     for (long long t = blockIdx.x; t < tiles; t += nblk) {
@@ -2844,14 +2851,14 @@ __global__ __launch_bounds__(kRedBlock) void fermi_round_kernel(const FermiSnap 
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
                 const int k = k0 - 4 * u;
-                x[u] = k >= 0 ? (z * f.rk[k < 0 ? 0 : k] + c - mu) * rkt : 2.0 * kFarX;
-                on[u] = !__all(x[u] > kFarX);
+                x[u] = k >= 0 ? (z * f.rk[k < 0 ? 0 : k] + c - mu) * rkt : 2.0 * kZeroX;
+                on[u] = !__all(x[u] > far);
                 wk[u] = on[u] ? w[k * f.nd] : 0.0;
             }
 #pragma unroll
             for (int u = 0; u < 4; ++u)
                 if (on[u]) {
-                    const double g = __all(x[u] < -kFarX) ? 1.0 : fermi_fn(x[u]);
+                    const double g = __all(x[u] < -kOneX) ? 1.0 : fermi_fn(x[u]);
                     acc += valid ? g * wk[u] : 0.0;
                 }
         }
@@ -2888,7 +2895,7 @@ __global__ __launch_bounds__(kRedBlock) void density_kernel(const double *mom, c
                                                             double *rho, double *partials) {
     extern __shared__ double rows[];
     __shared__ double sh[kRedBlock / 64];
-    const double mu = mu_dev ? *mu_dev : mu_arg, rkt = 1.0 / kT;
+    const double mu = mu_dev ? *mu_dev : mu_arg, rkt = reciprocal_kt(kT);
     const int l = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const long long tiles = (nd + kTileNodes - 1) / kTileNodes;
     double eb = 0.0, en = 0.0, er = 0.0;
@@ -2911,7 +2918,7 @@ __global__ __launch_bounds__(kRedBlock) void density_kernel(const double *mom, c
                 const bool in = k < nq;
                 const double lam = z * rk[in ? k : 0] + c, x = (lam - mu) * rkt;
                 double g, e;
-                if (__all(!in || fabs(x) > kFarX)) {
+                if (__all(!in || fabs(x) > kZeroX)) {
                     g = x > 0.0 ? 0.0 : 1.0;
                     e = 0.0;
                 } else {
