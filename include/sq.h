@@ -262,8 +262,9 @@ int sq_batch_step(sq_batch *batch, double *mu, double *energies, void *stream);
  * together) and keep the fastest; then, at that tile, time every kernel shape
  * (SQ_SHAPE_* combinations) each launch group's cube side has, that group
  * alone, and keep its fastest.  With cache_path (host, may be NULL) the
- * choice is read from / appended to that JSON file, keyed by the device and
- * the batch's cube sizes, chain counts and precision.  Invalidates a captured
+ * choice is read from / appended to that JSON file, keyed by the device, the
+ * library's kernel generation and the batch's cube sizes, chain counts and
+ * precision (entries of other generations are left alone).  Invalidates a captured
  * graph.  Synchronises `stream`. */
 int sq_batch_autotune(sq_batch *batch, const char *cache_path, void *stream);
 

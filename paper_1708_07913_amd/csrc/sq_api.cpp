@@ -759,8 +759,9 @@ std::string tune_key(const sq_batch *b) {
         parts.push_back("C" + std::to_string(g.C) + "x" + std::to_string(g.nch) + ":" + std::to_string(nodes));
     }
     std::sort(parts.begin(), parts.end());
-    // "lms": timed on the Lanczos and moments launches together, with kernel shapes
-    std::string key = std::string(b->device_name) + "/" + std::to_string(b->cus) + "cu/lms/" + (b->mixed ? "mixed" : "fp64");
+    // "lms": timed on the Lanczos and moments launches together, with kernel shapes of this generation
+    std::string key = std::string(b->device_name) + "/" + std::to_string(b->cus) + "cu/lms" +
+                      std::to_string(sq::kShapeGeneration) + "/" + (b->mixed ? "mixed" : "fp64");
     for (const auto &p : parts) key += "/" + p;
     return key;
 }

@@ -99,6 +99,10 @@ constexpr bool has_two_plane_shape(int C) { return C >= 21 && C <= kResidentCube
 // one-plane kernels instead, whose half as many plane buffers leave room for a
 // second workgroup on the CU.
 constexpr bool two_plane_kernels(int C, int two) { return has_two_plane_shape(C) && !(two && default_two_rows(C)); }
+// What the bits select, for caches of tuned shapes: raised whenever a cube side's
+// kernels for some bits, or the workgroups of them that a CU holds, change (2: patch
+// kernels and two-row defaults behind shape 0), so that older entries are tuned anew.
+constexpr int kShapeGeneration = 2;
 // Variants that exist for cube side C (a subset of the bits above).
 constexpr int shape_variants(int C) {
     return (has_two_row_shape(C) ? kShapeTwoRows : 0) | (has_two_plane_shape(C) ? kShapeTwoPlanes : 0);
