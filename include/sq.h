@@ -221,12 +221,19 @@ typedef struct sq_batch_options {
                             amplify past 1, which at low n_pl a moderate escape
                             need not do. */
     int shape;           /* SQ_SHAPE_* bits for the recurrence launches of every cube
-                            side that has them (other sides ignore them); 0 (default):
-                            one cube column per thread and one plane per barrier.
+                            side that has them (other sides ignore them).  0 (default):
+                            the kernels that single contexts run: for FP64 two cube
+                            columns per thread on 17-21 points, patches of 2 x 2
+                            columns on 25-31 points where no two projector spheres
+                            overlap, otherwise one column per thread up to 27 points
+                            and two on 29 and 31; one plane per barrier.
                             sq_batch_autotune chooses them per launch group. */
 } sq_batch_options;
 
-/* Kernel shapes of the batched recurrence launches (bits of sq_batch_options.shape). */
+/* Kernel shapes of the batched recurrence launches (bits of sq_batch_options.shape).
+ * On 21 points SQ_SHAPE_TWO_ROWS is the FP64 default and has one plane per barrier,
+ * also with SQ_SHAPE_TWO_PLANES.  Any bit takes 25-31-point groups to the kernels
+ * that work column by column. */
 #define SQ_SHAPE_TWO_ROWS 1   /* two y-adjacent cube columns per thread: 21-27-point cubes */
 #define SQ_SHAPE_TWO_PLANES 2 /* two cube planes per workgroup barrier in the FP64 Lanczos
                                  and moments sweeps: 21-31-point cubes */

@@ -1531,6 +1531,11 @@ int sq_batch_autotune(sq_batch *b, const char *cache_path, void *stream) {
                 double best_g = 1e300;
                 for (int sh = 0; sh < 4 && !rc; ++sh) {
                     if (sh & ~variants) continue;
+                    const int same = sq::same_kernels_shape(g.C, sh, b->mixed);
+                    if (same != sh) {
+                        t.ms[sh] = t.ms[same];
+                        continue;
+                    }
                     g.set_shape(sh);
                     float ms = 0.f, ms2 = 0.f;
                     rc = timed(gi, &ms);

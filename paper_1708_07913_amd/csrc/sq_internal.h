@@ -108,6 +108,13 @@ constexpr int shape_variants(int C) {
     return (has_two_row_shape(C) ? kShapeTwoRows : 0) | (has_two_plane_shape(C) ? kShapeTwoPlanes : 0);
 }
 
+// The least shape bits with the same kernels as `shape`: on 21 points the two-row
+// build has one plane a barrier and is the FP64 default.
+constexpr int same_kernels_shape(int C, int shape, bool mixed) {
+    if (default_two_rows(C) && (shape & kShapeTwoRows)) return mixed ? kShapeTwoRows : 0;
+    return shape;
+}
+
 // Projector runs of a region that the recurrence kernels accept.
 constexpr int max_region_runs(int C) { return (C > kResidentCube ? 4 : 6) * C * C + 512; }
 

@@ -42,3 +42,18 @@ def test_entries_without_the_generation_are_tuned_anew(tmp_path):
     assert t["block_nodes"] in (8, 32, 128)
     data = json.load(open(cache))
     assert data[old] == entry and len(data) == 2
+
+
+@pytest.mark.parametrize("precision,same", [("fp64", [(0, 1), (0, 3)]), ("mixed", [(1, 3)])])
+def test_shapes_with_the_same_kernels_are_timed_once(tmp_path, precision, same):
+    """21-point cubes: the two-row build is the FP64 default and has one plane a
+    barrier.  Shape bits with the same kernels share one sample time (a second
+    measurement hardly ever gives the same microseconds)."""
+    wl = W.fcc_workload("c21", 2, 7.78, 0.1, 31, 0.5, 5.0, 24, 1.0, precision=precision)
+    cache = str(tmp_path / "tiles.json")
+    _batch(wl).autotune(cache)
+    (entry,) = json.load(open(cache)).values()
+    (cube, _, *ms), = entry["shape_ms"]
+    assert cube == 21 and all(t > 0 for t in ms)
+    assert all(ms[a] == ms[b] for a, b in same), ms
+    assert entry["shapes"][0][2] not in [b for _, b in same]
