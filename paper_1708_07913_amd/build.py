@@ -11,6 +11,8 @@ r^2 <= r_c^2 must be evaluated exactly as written).
 from __future__ import annotations
 
 import os
+import re
+import shutil
 import subprocess
 import sys
 from concurrent.futures import ThreadPoolExecutor
@@ -46,8 +48,44 @@ TWO_ROW_GROUPS = [[17, 19], [21], [23], [25], [27]]
 # execution mask by itself: with the compiler's pass that merges such ends, a
 # constant that was rematerialised after a masked loop fell in front of the
 # merged restore, was written with an empty mask, and a wild LDS address followed.
+# The source does not compile without the macro; the pattern itself is looked for in
+# the generated code of every kernel (masked_writes).
 TILE_CUBES = [25, 27, 29, 31]
-TILE_FLAGS = ["-mllvm", "-amdgpu-remove-redundant-endcf=0"]
+TILE_FLAGS = ["-mllvm", "-amdgpu-remove-redundant-endcf=0", "-DSQ_KEEP_BRANCH_ENDS"]
+
+
+def masked_writes(listing: str) -> list[str]:
+    """Vector instructions of an AMDGPU listing that stand between a point which can
+    be reached with an empty execution mask (the way out of a masked loop, the target
+    of an s_cbranch_execz) and the next write of the mask."""
+    lines = listing.split("\n")
+    # Branches that depend on the mask stand behind the instruction that may empty it.
+    # (Others, in uniform regions, only mark a way that is always or never taken.)
+    mask = r"^\s*s_\w*(?:saveexec\w* .*|\w+ exec,.*)\n\s*s_cbranch_exec"
+    skipped_to = set(re.findall(mask + r"z (\S+)", listing, re.M))
+    ways_back = {listing.count("\n", 0, m.end()) + 1 for m in re.finditer(mask + "nz", listing, re.M)}
+    found, labels, empty = [], set(), False
+    for number, line in enumerate(lines, 1):
+        label = re.match(r"(\S+):", line)
+        if label:
+            if label.group(1).startswith(".LBB"):
+                labels.add(label.group(1))
+                empty = empty or label.group(1) in skipped_to
+            else:
+                labels, empty = set(), False
+            continue
+        text = line.split(";")[0].split()
+        if not text:
+            continue
+        op, rest = text[0], text[1:]
+        if number in ways_back and rest[0] in labels:
+            empty = True
+        elif "saveexec" in op or op in ("s_branch", "s_endpgm", "s_cbranch_execz") or \
+                (op.startswith("s_") and rest and rest[0].startswith("exec")):
+            empty = False
+        elif empty and re.match(r"(v_(?!readlane|writelane|readfirstlane)|ds_|buffer_|global_|flat_|scratch_)", op):
+            found.append(f"{number}: {' '.join(text)}")
+    return found
 
 
 def _run(cmd):
@@ -58,32 +96,42 @@ def _run(cmd):
     return r
 
 
+def _compile(cmd, obj):
+    """Compile one object; the listing of its device code, if there is one, must pass
+    masked_writes."""
+    tmp = obj + ".dir"
+    os.makedirs(tmp, exist_ok=True)
+    r = _run([*cmd, "-save-temps=obj", "-c", "-o", os.path.join(tmp, "out.o")])
+    for name in os.listdir(tmp):
+        if name.endswith(f"{ARCH}.s"):
+            with open(os.path.join(tmp, name)) as f:
+                found = masked_writes(f.read())
+            if found:
+                raise RuntimeError(f"{tmp}/{name}: vector instructions behind an empty execution mask: "
+                                   + "; ".join(found[:5]))
+    os.replace(os.path.join(tmp, "out.o"), obj)
+    shutil.rmtree(tmp)
+    return r
+
+
 def build(verbose: bool = False, jobs: int | None = None) -> str:
     os.makedirs(BUILD, exist_ok=True)
     jobs = jobs or min(8, os.cpu_count() or 1)
-    cmds = []
-    objs = []
     src_k = os.path.join(CSRC, "sq_kernels.hip")
+    src_t = os.path.join(CSRC, "sq_tile_kernels.hip")
     parts = [(g, 0) for g in CUBE_GROUPS] + [(g, 1) for g in TWO_ROW_GROUPS]
+    work = []  # (command, object)
     for i, (group, two) in enumerate(parts):
         cubes = " ".join(f"X({c})" for c in group)
-        obj = os.path.join(BUILD, f"sq_kernels_{i}.o")
         defs = [f"-DSQ_CUBES={cubes}", "-DSQ_PART=%d" % i, "-DSQ_TWO_ROWS=%d" % two]
-        cmds.append([HIPCC, *DEVICE_FLAGS, *defs, "-c", src_k, "-o", obj])
-        objs.append(obj)
+        work.append(([HIPCC, *DEVICE_FLAGS, *defs, src_k], f"sq_kernels_{i}.o"))
     for c in reversed(TILE_CUBES):
-        obj = os.path.join(BUILD, f"sq_tile_{c}.o")
-        cmds.append([HIPCC, *DEVICE_FLAGS, *TILE_FLAGS, f"-DSQ_CUBES=X({c})", "-c", os.path.join(CSRC, "sq_tile_kernels.hip"),
-                     "-o", obj])
-        objs.append(obj)
-    obj = os.path.join(BUILD, "sq_common.o")
-    cmds.append([HIPCC, *DEVICE_FLAGS, "-DSQ_COMMON_ONLY", "-c", src_k, "-o", obj])
-    objs.append(obj)
-    obj = os.path.join(BUILD, "sq_api.o")
-    cmds.append([CXX, *HOST_FLAGS, "-c", os.path.join(CSRC, "sq_api.cpp"), "-o", obj])
-    objs.append(obj)
+        work.append(([HIPCC, *DEVICE_FLAGS, *TILE_FLAGS, f"-DSQ_CUBES=X({c})", src_t], f"sq_tile_{c}.o"))
+    work.append(([HIPCC, *DEVICE_FLAGS, "-DSQ_COMMON_ONLY", src_k], "sq_common.o"))
+    work.append(([CXX, *HOST_FLAGS, os.path.join(CSRC, "sq_api.cpp")], "sq_api.o"))
+    objs = [os.path.join(BUILD, name) for _, name in work]
     with ThreadPoolExecutor(jobs) as ex:
-        for r in ex.map(_run, cmds):
+        for r in ex.map(_compile, [cmd for cmd, _ in work], objs):
             if verbose and r.stderr:
                 sys.stderr.write(r.stderr)
     tmp = LIB + ".tmp"

@@ -18,6 +18,9 @@
 // one of them; its projector value is read from a periodic grid like V_eff, and
 // a byte per cube point (LDS) names the region's image.  A point outside every
 // sphere has the value 0 and may carry any label.
+#ifndef SQ_KEEP_BRANCH_ENDS
+#error "compile with -mllvm -amdgpu-remove-redundant-endcf=0 -DSQ_KEEP_BRANCH_ENDS (see TILE_FLAGS in build.py for why)"
+#endif
 #include "sq_device.h"
 
 #include <type_traits>
