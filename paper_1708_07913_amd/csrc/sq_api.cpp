@@ -65,7 +65,7 @@ struct sq_ctx {
     std::vector<double> ctab, rk;
     double start_norm = 0;
     int device = 0;
-    int nwg_lanczos = 0, nwg_moments = 0, nwg_forces = 0, nwg_slots = 0;
+    int nwg_lanczos = 0, nwg_moments = 0, nwg_forces = 0, nwg_slots = 0;  // nwg_forces: from the first force call on
     int nch = 2;        // projector chains per cube column (max sphere overlap depth)
     int pstride = 0;    // doubles between a projector value and the one a plane above
     int max_overlap = 0;
@@ -300,24 +300,38 @@ int pick_workgroups(sq_ctx *c) {
     rc = hip_check(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev), "CU count");
     if (rc) return rc;
     const bool mixed = c->opt.precision == SQ_FP32_MIXED;
-    int bl = 0, bm = 0, bf = 0;
+    int bl = 0, bm = 0;
     rc = hip_check(sq::recurrence_occupancy(c->C, true, mixed, c->nch, &bl), "occupancy (Lanczos)");
     if (rc) return rc;
     rc = hip_check(sq::recurrence_occupancy(c->C, false, mixed, c->nch, &bm), "occupancy (moments)");
     if (rc) return rc;
-    rc = hip_check(sq::forces_occupancy(c->C, c->nch, &bf), "occupancy (forces)");
-    if (rc) return rc;
-    if (bl < 1 || bm < 1 || bf < 1) return fail(SQ_EDEVICE, "recurrence kernel does not fit on a compute unit");
+    if (bl < 1 || bm < 1) return fail(SQ_EDEVICE, "recurrence kernel does not fit on a compute unit");
     auto round8 = [](long long v) { return int(std::max<long long>(8, (v + 7) / 8 * 8)); };
     const long long cap = (c->nd + 7) / 8 * 8;
     if (c->opt.workgroups > 0) {
-        c->nwg_lanczos = c->nwg_moments = c->nwg_forces = round8(c->opt.workgroups);
+        c->nwg_lanczos = c->nwg_moments = round8(c->opt.workgroups);
     } else {
         c->nwg_lanczos = round8(std::min<long long>(cap, (long long)cus * bl / 8 * 8));
         c->nwg_moments = round8(std::min<long long>(cap, (long long)cus * bm / 8 * 8));
-        c->nwg_forces = round8(std::min<long long>(cap, (long long)cus * bf / 8 * 8));
     }
-    c->nwg_slots = std::max({c->nwg_lanczos, c->nwg_moments, c->nwg_forces});
+    c->nwg_slots = std::max(c->nwg_lanczos, c->nwg_moments);
+    return SQ_OK;
+}
+
+// Workgroups of the force kernel: as many as are resident, within the Lanczos launch's
+// (whose two buffers per workgroup it uses).  Asked for at the first force call: on
+// 17-21 points the kernel's code object, which set-up would load for the question
+// alone, is not the FP64 recurrences' (set-up 2.0 -> 3.3 ms).
+int force_workgroups(sq_ctx *c, int *nwg) {
+    if (c->nwg_forces == 0) {
+        int cus = 0, bf = 0;
+        int rc = hip_check(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device), "CU count");
+        if (!rc) rc = hip_check(sq::forces_occupancy(c->C, c->nch, &bf), "occupancy (forces)");
+        if (rc) return rc;
+        if (bf < 1) return fail(SQ_EDEVICE, "force kernel does not fit on a compute unit");
+        c->nwg_forces = c->opt.workgroups > 0 ? c->nwg_lanczos : std::min(c->nwg_lanczos, std::max(8, cus * bf / 8 * 8));
+    }
+    *nwg = c->nwg_forces;
     return SQ_OK;
 }
 
@@ -349,9 +363,8 @@ void layout(sq_ctx *c) {
     // streamed regions (wider than kResidentCube) need a second buffer in the
     // moments sweep and a third in Lanczos
     const bool stream = c->C > sq::kResidentCube;
-    const int nwg_two = std::max(c->nwg_lanczos, c->nwg_forces);  // launches with a second buffer
-    c->off_wslots = take(size_t(stream ? c->nwg_slots : nwg_two) * se * sizeof(double));
-    c->off_xslots = take(stream ? size_t(nwg_two) * se * sizeof(double) : 0);
+    c->off_wslots = take(size_t(stream ? c->nwg_slots : c->nwg_lanczos) * se * sizeof(double));
+    c->off_xslots = take(stream ? size_t(c->nwg_lanczos) * se * sizeof(double) : 0);
     c->off_brent = take(sizeof(sq::BrentState));
     c->total = off;
 }
@@ -1226,7 +1239,10 @@ int sq_nl_forces(sq_ctx *c, double mu, double *forces, void *stream) {
         sq::LaunchArgs k;
         rc = stage_launch(c, a, 1, s, &k);
         if (rc) return rc;
-        rc = hip_check(sq::launch_forces(k, c->C, c->nch, c->nwg_forces, s), "launching forces");
+        int nwg = 0;
+        rc = force_workgroups(c, &nwg);
+        if (rc) return rc;
+        rc = hip_check(sq::launch_forces(k, c->C, c->nch, nwg, s), "launching forces");
         if (rc) return rc;
         rc = hip_check(hipMemcpyAsync(forces, fdev, 3 * na * sizeof(double), hipMemcpyDeviceToHost, s),
                        "reading forces");
