@@ -14,13 +14,13 @@ constexpr int kMaxLanczos = 256; // Lanczos steps per node
 constexpr int kMaxCube = 37;     // largest cube side (region of influence)
 constexpr int kResidentCube = 31; // largest cube side whose columns stay in registers
 
-// Rows of the cube owned by one thread of the recurrence kernels: one column
-// up to 27 points (a workgroup of C^2 threads, 7-12 waves for 21-27 points),
-// two y-adjacent columns for 29 and 31 points (512-thread workgroups, 256
-// VGPRs per lane; the pair shares its y-neighbour reads), three beyond 31
-// points.  One row on 29 points spills.  The 21-27-point cubes also have a
-// two-row shape (`two` = 1: 32-lane row groups, 6-7 waves), built as a
-// separate set of kernels that batches may select (kShapeTwoRows).
+// Rows of the cube owned by one thread of the recurrence kernels that work column by
+// column: one up to 27 points (a workgroup of C^2 threads, 7-12 waves for 21-27
+// points), two y-adjacent ones on 29 and 31 points (512-thread workgroups, 256 VGPRs
+// per lane; the pair shares its y-neighbour reads), three beyond 31 points.  One row
+// on 29 points spills.  A second build (`two` = 1) has two rows on 17-27 points: on
+// 21-27 as a shape that batches may select (kShapeTwoRows; 32-lane row groups on
+// 23-27, 6-7 waves), on 17-21 as the FP64 default (default_two_rows).
 constexpr bool has_two_row_shape(int C) { return C >= 21 && C <= 27; }
 // Cubes whose FP64 recurrences run the two-row build by default.  One column a
 // thread is 5 to 7 waves, of which a CU holds one workgroup; two are 3 or 4, and

@@ -44,7 +44,7 @@ constexpr int NO = kNoMax;
 #ifndef SQ_LANCZOS_AHEAD
 #define SQ_LANCZOS_AHEAD 1
 #endif
-// Two-row build of the 21-27-point cubes (a second object of this file; its
+// Two-row build of the 17-27-point cubes (a second object of this file; its
 // kernels live in namespace sq::two_rows, opened above when the build defines
 // SQ_TWO_ROWS=1; left undefined, the preprocessor reads it as 0 there)
 #ifndef SQ_TWO_ROWS
@@ -3008,17 +3008,24 @@ hipError_t with_chains(int nch, F &&f) {
     }
 }
 // Planes per barrier of the ring kernels for shape bits `shape`, and the chain
-// counts built for it.
-template <int c, bool single, typename F>
+// counts built for it.  `one_plane`: launches reach the kernels with one plane a
+// barrier.
+template <int c, bool single, bool one_plane, typename F>
 hipError_t with_shape(int nch, int shape, F &&f) {
     if constexpr (two_plane_kernels(c, SQ_TWO_ROWS))
         if (shape & kShapeTwoPlanes)
             return with_chains<c, true>(nch, [&](auto n) { return f(n, std::integral_constant<int, 2>()); });
-    return with_chains<c, single || SQ_TWO_ROWS>(nch, [&](auto n) { return f(n, std::integral_constant<int, 1>()); });
+    if constexpr (one_plane)
+        return with_chains<c, single || SQ_TWO_ROWS>(nch, [&](auto n) { return f(n, std::integral_constant<int, 1>()); });
+    else
+        return hipErrorInvalidValue;
 }
+// FP64 moments with one column a thread: not where two are the default.
+template <int c>
+constexpr bool kOnePlaneMoments = SQ_TWO_ROWS || !default_two_rows(c);
 template <int c>
 hipError_t launch_lanczos_t(const LaunchArgs &a, int nch, int nwg, hipStream_t s, int shape) {
-    return with_shape<c, true>(nch, shape, [&](auto ncht, auto ppbt) {
+    return with_shape<c, true, true>(nch, shape, [&](auto ncht, auto ppbt) {
         constexpr int NCH = decltype(ncht)::value, PPB = decltype(ppbt)::value;
         if constexpr (!Shape<c>::STREAM)
             hipLaunchKernelGGL((lanczos_ring_kernel<c, NCH, PPB>), dim3(nwg), dim3(Shape<c>::BLOCK), 0, s, a);
@@ -3038,7 +3045,7 @@ hipError_t launch_moments_t(const LaunchArgs &a, int nch, bool mixed, int nwg, h
                                    s, a);
                 return hipGetLastError();
             });
-    return with_shape<c, false>(nch, shape, [&](auto ncht, auto ppbt) {
+    return with_shape<c, false, kOnePlaneMoments<c>>(nch, shape, [&](auto ncht, auto ppbt) {
         constexpr int NCH = decltype(ncht)::value, PPB = decltype(ppbt)::value;
         if constexpr (!Shape<c>::STREAM)
             hipLaunchKernelGGL((moments_ring_kernel<c, NCH, PPB>), dim3(nwg), dim3(Shape<c>::BLOCK), 0, s, a);
@@ -3074,7 +3081,7 @@ template <int c>
 hipError_t occupancy_t(bool lanczos, bool mixed, int nch, int *nb, int shape) {
     const int B = Shape<c>::BLOCK;
     if (lanczos)
-        return with_shape<c, true>(nch, shape, [&](auto ncht, auto ppbt) {
+        return with_shape<c, true, true>(nch, shape, [&](auto ncht, auto ppbt) {
             constexpr int NCH = decltype(ncht)::value, PPB = decltype(ppbt)::value;
             if constexpr (!Shape<c>::STREAM)
                 return hipOccupancyMaxActiveBlocksPerMultiprocessor(nb, lanczos_ring_kernel<c, NCH, PPB>, B, 0);
@@ -3087,7 +3094,7 @@ hipError_t occupancy_t(bool lanczos, bool mixed, int nch, int *nb, int shape) {
                 return hipOccupancyMaxActiveBlocksPerMultiprocessor(nb, moments_mixed_kernel<c, decltype(ncht)::value>, B,
                                                                     0);
             });
-    return with_shape<c, false>(nch, shape, [&](auto ncht, auto ppbt) {
+    return with_shape<c, false, kOnePlaneMoments<c>>(nch, shape, [&](auto ncht, auto ppbt) {
         constexpr int NCH = decltype(ncht)::value, PPB = decltype(ppbt)::value;
         if constexpr (!Shape<c>::STREAM)
             return hipOccupancyMaxActiveBlocksPerMultiprocessor(nb, moments_ring_kernel<c, NCH, PPB>, B, 0);
