@@ -1295,7 +1295,9 @@ int sq_batch_create(sq_batch **out, sq_ctx *const *ctxs, int n, double *const *m
             b->n_e.push_back(n_electrons[i]);
             b->max_brent = i == 0 ? c->opt.max_brent : std::max(b->max_brent, c->opt.max_brent);
             // slots hold the layout of any shape the autotuner may pick
-            b->max_slot = std::max({b->max_slot, sq::slot_elems_for(c->C, 0), sq::slot_elems_for(c->C, 1)});
+            // (an even number, so that every workgroup's slot is aligned for 16-byte accesses)
+            b->max_slot = std::max({b->max_slot, (sq::slot_elems_for(c->C, 0) + 1) & ~1LL,
+                                    (sq::slot_elems_for(c->C, 1) + 1) & ~1LL});
             // one launch per cube side and chain count
             auto g = std::find_if(b->groups.begin(), b->groups.end(),
                                   [&](const sq_batch::Group &x) { return x.C == c->C && x.nch == c->nch; });
