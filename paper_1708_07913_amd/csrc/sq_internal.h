@@ -54,18 +54,19 @@ constexpr long long slot_plane(int C, int two = 0) {
                                    rows_per_thread(C, two);
 }
 // FP64 recurrences of the patch kernels (sq_tile_kernels.hip): cubes of 25 points
-// and more whose spheres do not overlap.  Per recurrence step with 256
-// workgroups, ring kernels -> patch kernels (us; bounds, moments):
-//   25 points  27.4 22.2 -> 24.3 21.6
-//   27 points  32.4 26.0 -> 26.6 23.2
-//   29 points  40.4 35.2 -> 30.5 27.9
-//   31 points  44.1 40.3 -> 35.4 30.9
+// and more whose spheres do not overlap.  Per recurrence step with 256 workgroups
+// (32^3 nodes), ring kernels -> patch kernels (us; bounds, moments):
+//   25 points  27.5 21.5 -> 24.6 20.4
+//   27 points  32.6 25.4 -> 27.2 22.4
+//   29 points  40.3 35.3 -> 29.5 25.7
+//   31 points  43.9 40.0 -> 34.3 26.9
 // Below 25 points a patch would leave more lanes idle than it saves; with a
 // second projector layer the registers spill (29 points: 48.5 48.6 -> 59.0
-// 45.8).  FP32-mixed contexts keep the ring kernels for both: their rounding
-// turns a last bit of difference in a sum or in a bound into one of 6e-8 in the
-// density of single nodes, and the ring kernels' order of summation costs the
-// patch kernels what they gain (27 points: 30.2 against 27.7).
+// 45.8).  FP32-mixed contexts keep the ring kernels for both: there a last bit of a
+// sum or of a bound can turn a rounding of the stored vector, up to 6e-8 in the
+// density of single nodes (two runs differ by that in a few cells of a hundred, with
+// the order in which the projector dots arrive), and other kernels would move every
+// cell's results by as much.
 constexpr bool tile_cube(int C, int nch) { return C >= 25 && C <= kResidentCube && nch == 1; }
 // A thread's patch there: two x-adjacent by kPatchRows y-adjacent cube columns.
 constexpr int kPatchRows = 2;

@@ -141,6 +141,9 @@ struct Lds {
     int item; // work-queue index taken by the workgroup
 };
 
+// Where registers limit the workgroups (17 points and more) the tables keep places of
+// their own, in this order: with the order above the bounds of 23-point cubes took
+// 199.9 ms instead of 196.1.
 template <int C, typename T, int NCH>
 struct Lds<C, T, NCH, false> {
     T plane[Shape<C>::NBUF][Shape<C>::PLANE];
@@ -2665,8 +2668,8 @@ __device__ __forceinline__ void weight_tiles(const double *row, bool valid, cons
     }
 }
 
-// W[k][q] of all nodes.  1.3e6 nodes, N_q 65: the moments are read and W written
-// once (1.35 GB).
+// W[k][q] of all nodes.  1.3e6 nodes, N_q 65: 0.92 ms, of which reading the moments
+// and writing W once (1.35 GB) would take 0.28; bound like density_kernel.
 template <bool STAGED>
 __global__ __launch_bounds__(kRedBlock) void weights_kernel(const double *mom, const double *ctab, double *W,
                                                             long long nd, int nq) {
@@ -2693,10 +2696,11 @@ __global__ __launch_bounds__(kRedBlock) void weights_kernel(const double *mom, c
 }
 
 // Fermi function g and entropy term of x = (lambda - mu) / kT.  A wave whose lanes
-// all lie far from 0 takes no exponential.  Up to x = -kOneX, 1 + exp(x) rounds to 1,
-// so g is 1; beyond |x| = kZeroX, exp(-|x|) is 0, so g is 0 or 1 and the entropy 0.
-// The density takes mu as it is given, also far outside the spectrum, where every
-// term is small: it leaves out only what is exactly 0.
+// all lie far from 0 takes no exponential, or no logarithm and quotient.  Beyond
+// |x| = kOneX, 1 + exp(-|x|) rounds to 1, so g is 1 below -kOneX; beyond |x| =
+// kZeroX, exp(-|x|) is 0, so g is 0 or 1 and the entropy 0.  The density takes mu as
+// it is given, also far outside the spectrum, where every term is small: it leaves
+// out only what is exactly 0.
 constexpr double kOneX = 37.0, kZeroX = 746.0;
 __device__ __forceinline__ double reciprocal_kt(double kT) { return fmin(1.0 / kT, 1.7976931348623157e308); }
 __device__ __forceinline__ double fermi_fn(double x) { return 1.0 / (1.0 + exp(x)); }
@@ -2886,8 +2890,11 @@ __global__ __launch_bounds__(kRedBlock) void fermi_round_kernel(const FermiSnap 
 // Density and energies straight from the moments: a wave forms W of 16 nodes on
 // the matrix cores and uses it where it stands, 4 quadrature points a lane; no
 // N_d x N_q buffer is written or read.  Per-block partials of {E_band, E_ent,
-// sum rho} go to `partials`.  1.3e6 nodes, N_q 65: bounded by the moments' bytes
-// (0.68 GB) and the contraction (0.19 ms each at this card's rates).
+// sum rho} go to `partials`.  1.3e6 nodes, N_q 65: 1.0-1.5 ms by how many points
+// need an exponential.  The moments' bytes (0.68 GB) and the matrix instructions
+// would take 0.14 and 0.19 ms: for every 16 nodes a wave reads the whole c-table and
+// runs one chain of dependent matrix instructions, and most of its time waits for
+// them.
 template <bool STAGED>
 __global__ __launch_bounds__(kRedBlock) void density_kernel(const double *mom, const double *ctab, const double *chi,
                                                             const double *zeta, const double *rk, long long nd, int nq,
@@ -2922,9 +2929,15 @@ __global__ __launch_bounds__(kRedBlock) void density_kernel(const double *mom, c
                     g = x > 0.0 ? 0.0 : 1.0;
                     e = 0.0;
                 } else {
-                    const double ax = fabs(x), ex = exp(-ax), d = 1.0 / (1.0 + ex);
-                    g = x > 0.0 ? ex * d : d;
-                    e = -(log1p(ex) + ax * ex * d);
+                    const double ax = fabs(x), ex = exp(-ax);
+                    if (__all(!in || ax > kOneX)) {  // 1 + ex rounds to 1, log1p(ex) to ex
+                        g = x > 0.0 ? ex : 1.0;
+                        e = -(ex + ax * ex);
+                    } else {
+                        const double d = 1.0 / (1.0 + ex);
+                        g = x > 0.0 ? ex * d : d;
+                        e = -(log1p(ex) + ax * ex * d);
+                    }
                 }
                 if (in) {
                     sg += g * w[r];

@@ -642,11 +642,11 @@ __device__ __forceinline__ void unit_vector(const AT &A, LdsT &L, Vec<C> &X, lon
 }
 
 // ---------------------------------------------------------------------------
-// Chebyshev moments.  29-point cubes, 256 workgroups: 27.9 us a step (ring kernel
-// 35.2).  Of the 2000 cycles of a plane the FP64 pipe is busy for 880 (718 are the
-// stencil's and the recurrence's own), another 400 issue LDS, memory and scalar
-// instructions, and a quarter waits for LDS and the barrier: with 490 registers a
-// SIMD holds one wave, which hides only what the batches hide.
+// Chebyshev moments.  29-point cubes, 256 workgroups: 25.7 us a step (ring kernel
+// 35.3), 2040 cycles a plane.  Of a wave's cycles 45 % issue vector instructions (about
+// 175 FP64 ones a plane), 10 % LDS and 9 % other instructions, 22 % wait for LDS, memory
+// and the barrier and 14 % for an instruction's turn: with 512 registers a SIMD holds
+// one wave, which hides only what the batches hide.
 // ---------------------------------------------------------------------------
 template <int C>
 __global__ __launch_bounds__(Tile<C>::BLOCK, 1) void moments_tile_kernel(LaunchArgs K) {
@@ -730,8 +730,8 @@ __global__ __launch_bounds__(Tile<C>::BLOCK, 1) void moments_tile_kernel(LaunchA
 // alpha'^2 > beta_j^2 / 4 on, both are summed from x_{j+1} itself (kCarried), and
 // below that line each step at least halves what it inherits.
 // Two vector transfers per step (x_{j-1} in, x_j out; the first planes in LDS);
-// 29-point cubes, 256 workgroups: 30.5 us a step (ring kernel, three transfers,
-// 40.4).
+// 29-point cubes, 256 workgroups: 29.5 us a step (ring kernel, three transfers,
+// 40.3).
 // ---------------------------------------------------------------------------
 constexpr double kCarried = 0.8;  // least beta_j^2 / |u_j|^2 at which sums are carried: 1 / (1 + 1/4)
 struct TileLanczos {
