@@ -69,10 +69,13 @@ typedef enum {
 enum { SQ_FP64 = 0, SQ_FP32_MIXED = 1 };
 
 typedef struct sq_options {
-    /* SQ_FP64: everything in FP64.  SQ_FP32_MIXED: recurrence vectors, potential
-     * window and stencil pair sums in FP32, every accumulation (stencil sum,
-     * projector dots, moments), the Lanczos bounds, coefficients, Fermi solve
-     * and energies in FP64. */
+    /* SQ_FP64: everything in FP64.  SQ_FP32_MIXED (cubes up to 31 points; wider
+     * ones run FP64): from the fifth Chebyshev step on the recurrence vectors are
+     * stored in FP32; all arithmetic, the Lanczos bounds, coefficients, Fermi solve
+     * and energies are FP64.  It halves the vectors' memory and is not faster.
+     * Results repeat to the last bits in FP64 and to about 1e-7 of the largest
+     * density in mixed mode, where a last bit of a sum (projector dots are added in
+     * the order in which they arrive) can turn a rounding of a stored value. */
     int precision;
     int n_lanczos;       /* Lanczos steps per node, 1..256 (default 50) */
     double margin;       /* zeta = (1 + margin)(l_max - l_min)/2 (default 0.05) */

@@ -18,10 +18,10 @@
 //     added into LDS at the run's end;
 //   * workgroups walk node ranges split by XCD (blockIdx % 8) so that one
 //     XCD's L2 holds neighbouring V_eff windows and projector tables.
-// FP32-mixed: vectors, LDS plane and potential window stored in FP32; every
-// operand is widened to FP64 before it is used, so the arithmetic (stencil
-// sum, projector terms, update, dots) is FP64 and the one rounding per step
-// is the FP32 store of t^{k+1}.
+// FP32-mixed: vectors stored in FP32; every operand is widened to FP64 before it
+// is used (the LDS plane and the potential are FP64), so the arithmetic (stencil
+// sum, projector terms, update, dots) is FP64 and the one rounding per step is the
+// FP32 store of t^{k+1}.
 #include "sq_device.h"
 
 #include <mutex>
